@@ -236,8 +236,18 @@ def prepare(case, seed):
     dt = torch.float64 if case["precision"] == "fp64" else torch.float32
     q, n = B.Q[p.lattice], int(np.prod(shape))
     bufs = [torch.empty((q, n), dtype=dt, device=DEV) for _ in range(2)]
-    h = B.sc_lbm_create(p, rho.ravel(), bufs[0].data_ptr(), bufs[1].data_ptr(), torch.cuda.current_stream().cuda_stream)
+    h = B.sc_lbm_create(p, rho.ravel(), bufs[0].data_ptr(), bufs[1].data_ptr(), _stream().cuda_stream)
     return dict(kind=kind, handle=_Handle(h), bufs=bufs, steps=case["steps"])
+
+
+_STREAM = []
+
+
+def _stream():
+    """The one stream the program steps its grids on, one after the other."""
+    if not _STREAM:
+        _STREAM.append(torch.cuda.Stream())
+    return _STREAM[0]
 
 
 class _Handle:
