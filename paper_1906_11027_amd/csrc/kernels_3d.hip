@@ -14,6 +14,7 @@
 // One barrier per plane: the 2R + 2 slots keep the next write away from the
 // 2R + 1 planes still being read.
 #include <algorithm>
+#include <cstdint>
 
 #include "kernels.h"
 
@@ -383,6 +384,9 @@ static const Shape3D kShapes3D[] = {
     // step) and fetches 1.40 of the algorithmic reads against 2.54
     {32, 8, 1, 64, "pmarch32x8r1h64pf1"},
     {32, 8, 1, 32, "pmarch32x8r1h32pf1"},
+    // the persistent marches with the segment height of balanced_height()
+    {64, 8, 1, 0, "pmarch64x8r1pf1"},
+    {32, 8, 1, 0, "pmarch32x8r1pf1"},
 };
 constexpr int kNumShapes3D = sizeof(kShapes3D) / sizeof(kShapes3D[0]);
 
@@ -401,13 +405,38 @@ static hipError_t launch_march(const StepArgs<T>& a, int H, hipStream_t s)
     return hipGetLastError();
 }
 
-// persistent march: one generation of blocks is what the device holds at once
+// Segment height of a persistent march over `cols` tile columns of nz planes
+// with `slots` resident blocks.  Every block of a generation walks its H
+// planes and the 2R planes of psi around them, so a step takes
+//   generations x (H + 2R),  generations = ceil(cols ceil(nz / H) / slots),
+// plane times; the height with the least is taken (the taller on a tie: less
+// is read twice).  Small grids get short segments, which put every CU to work
+// at the price of more overlap; large ones get tall segments whose count
+// fills the last generation.
+static int balanced_height(int64_t cols, int nz, int64_t slots, int R)
+{
+    int best = nz;
+    int64_t least = INT64_MAX;
+    // two segments per slot, or a few dozen to even out the last generation
+    const int64_t most = 2 * slots / cols + 32;
+    for (int segs = 1; segs <= nz && segs <= most; ++segs) {
+        const int H = (nz + segs - 1) / segs;
+        const int64_t gens = (cols * ((nz + H - 1) / H) + slots - 1) / slots;
+        const int64_t cost = gens * (H + 2 * R);
+        if (cost < least) {
+            least = cost;
+            best = H;
+        }
+    }
+    return best;
+}
+
+// persistent march: one generation of blocks is what the device holds at
+// once; H = 0 takes the balanced segment height
 template <typename T, int ORDER, bool MRT, int TX, int TYB, int RPT, int PF>
 static hipError_t launch_march_p(const StepArgs<T>& a, int H, hipStream_t s)
 {
-    if (H > a.nz) H = a.nz;
     const int nbx = (a.nx + TX - 1) / TX, nby = (a.ny + TYB * RPT - 1) / (TYB * RPT);
-    const int nitems = nbx * nby * ((a.nz + H - 1) / H);
     static int per_cu = 0, cus = 0;   // per process: one device type
     if (!per_cu) {
         int dev = 0, n = 0, c = 0;
@@ -421,6 +450,9 @@ static hipError_t launch_march_p(const StepArgs<T>& a, int H, hipStream_t s)
             return hipErrorUnknown;
         }
     }
+    if (H <= 0) H = balanced_height((int64_t)nbx * nby, a.nz, per_cu * cus, Stencil<3, ORDER>::R);
+    if (H > a.nz) H = a.nz;
+    const int nitems = nbx * nby * ((a.nz + H - 1) / H);
     const int nb = std::min(nitems, per_cu * cus);
     hipLaunchKernelGGL((k_d3q19_march_p<T, ORDER, MRT, TX, TYB, RPT, PF>), dim3(nb), dim3(TX, TYB), 0, s, a, H, nbx,
                        nby, nitems);
@@ -465,6 +497,8 @@ static hipError_t launch_v(const StepArgs<T>& a, int variant, hipStream_t s)
     case 20: return launch_march_p<T, ORDER, MRT, 64, 8, 1, 1>(a, 16, s);
     case 21: return launch_march_p<T, ORDER, MRT, 32, 8, 1, 1>(a, 64, s);
     case 22: return launch_march_p<T, ORDER, MRT, 32, 8, 1, 1>(a, 32, s);
+    case 23: return launch_march_p<T, ORDER, MRT, 64, 8, 1, 1>(a, 0, s);
+    case 24: return launch_march_p<T, ORDER, MRT, 32, 8, 1, 1>(a, 0, s);
     default: return hipErrorInvalidValue;
     }
 }

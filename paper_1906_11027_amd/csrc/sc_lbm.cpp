@@ -376,16 +376,33 @@ static void tune_store(const sc_lbm_params& p, int variant, double ms)
     std::fclose(f);
 }
 
+// D3Q19: the persistent march with balanced segments, on 64 x 8 tiles in
+// FP32 and 32 x 8 in FP64.  Its segment height follows the grid, so one shape
+// serves every size.  ms per step, MRT E8, against the one-segment shapes
+// that were taken before (march64x8r1h16pf1 in FP32, march32x16h16 in FP64):
+//   FP32   32^3 0.012 / 0.057, 64^3 0.016 / 0.053, 200 x 181 x 150 0.277 / 0.331,
+//          320^3 1.250 / 1.386, 128^3 0.085 / 0.086
+//   FP64   32^3 0.014 / 0.075, 64^3 0.030 / 0.151, 200 x 181 x 150 0.565 / 0.776,
+//          320^3 3.22 / 3.72, 128^3 0.203 / 0.200
+// FP32 rows of at most 32 nodes leave half of a 64-wide tile idle: 32 x 8
+// there (32^3: 0.010 ms).  The FP64 window of the 512-thread tile spills
+// except for SRT E4, where it is the faster on grids wide enough to fill it
+// (320^3: 2.17 / 2.61 ms).
+static int auto_variant_3d(const sc_lbm_params& p)
+{
+    constexpr int k64 = 23, k32 = 24;   // pmarch64x8r1pf1, pmarch32x8r1pf1
+    if (p.nx <= 32) return k32;
+    if (p.precision == SC_FP64) return p.collision == SC_SRT && p.order == 4 && p.nx >= 256 ? k64 : k32;
+    return k64;
+}
+
 static int auto_variant(const sc_lbm_params& p, int64_t n)
 {
     const int tuned = tune_lookup(p);
     if (tuned >= 0) return tuned;
     switch (family_of(p)) {
     case kFamD2Q9: return n < (int64_t)1 << 20 ? 2 : 0;   // tile32x8r1 / tile64x16r4
-    // march64x8r1h16pf1; in FP64 its 512-thread blocks leave 256 registers
-    // a lane and the E6/E8 MRT step spills, so FP64 takes the 256-thread
-    // march32x16h16, which keeps its window in registers
-    case kFamD3Q19: return p.precision == SC_FP64 ? 0 : 7;
+    case kFamD3Q19: return auto_variant_3d(p);
     default:
         if (n < (int64_t)1 << 20) return 1;                    // wide32x8r1
         // wide128x16r2; its 1024-thread blocks spill the FP64 D2Q25 step, which

@@ -1,0 +1,49 @@
+"""Launch shapes chosen by a rule, against the plain shapes of the same step.
+
+The shapes do the same arithmetic on the same values, but the compiler may
+fuse multiply-adds differently per shape: after k steps the states agree to a
+few roundings of their largest value per step (2e-6 in FP32 and 1e-14 in FP64
+relative to it over 6 steps)."""
+import numpy as np
+import pytest
+
+from tests.gpu_helpers import say
+from workload import droplet_rho
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():  # pragma: no cover
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_1906_11027_amd import Sim  # noqa: E402
+from paper_1906_11027_amd import sc_lbm as B  # noqa: E402
+
+
+def _state(rho0, lattice, steps, prec, variant, **kw):
+    sim = Sim(rho0, lattice, precision=prec, variant=variant, **kw)
+    sim.step(steps)
+    st, name = sim.state().astype(np.float64), sim.variant
+    sim.close()
+    return st, name
+
+
+def _agree(rho0, lattice, steps, prec, variant, plain, **kw):
+    st, name = _state(rho0, lattice, steps, prec, variant, **kw)
+    ref, rname = _state(rho0, lattice, steps, prec, plain, **kw)
+    d, top = float(np.max(np.abs(st - ref))), float(np.max(np.abs(ref)))
+    say("%s %s %s: %s vs %s max |diff| %.2e of %.2e" % (lattice, rho0.shape, prec, name, rname, d, top))
+    assert d <= (2e-6 if prec == "fp32" else 1e-14) * top
+
+
+# grids thinner than the psi window, one column, many columns, and a height
+# that the segments do not divide
+@pytest.mark.parametrize("shape", [(9, 7, 1), (33, 9, 2), (20, 17, 5), (70, 9, 131), (300, 40, 11)])
+@pytest.mark.parametrize("order,collision", [(4, "srt"), (8, "mrt")])
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+def test_balanced_march(shape, order, collision, prec):
+    """D3Q19 persistent marches with the balanced segment height (the
+    automatic shape and both tiles) against march32x8h16."""
+    rho0 = droplet_rho(shape, 3, seed=4)
+    n = B.sc_lbm_num_variants(B.make_params("D3Q19", shape))
+    for v in (-1, n - 2, n - 1):
+        _agree(rho0, "D3Q19", 6, prec, v, 2, order=order, collision=collision, tau=0.9)
