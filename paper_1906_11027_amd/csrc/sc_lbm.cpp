@@ -376,6 +376,83 @@ static void tune_store(const sc_lbm_params& p, int variant, double ms)
     std::fclose(f);
 }
 
+// D2Q9 with Guo forcing: the two-step tiles, which read and write the state
+// once per two steps and halve the launches.  us per step, E8 unless marked,
+// against the one-step shapes that were taken before (tile32x8r1 below 2^20
+// nodes, tile64x16r4 from there):
+//   up to about 330^2 the grid has few tiles per CU and latency counts: 32 x 8
+//     tiles with 1024 threads (256^2: FP32 2.57 / 3.64, FP64 3.34 / 4.62);
+//   FP32 beyond: 64 x 16, the smallest halo share (512^2 3.84 / 6.35, 2048^2
+//     43.7 / 78.3, 8192^2 638 / 1120).  At E10 its LDS leaves one block per CU
+//     and 32 x 32 is ahead (2048^2 48.9 / 63.5 for 64 x 16);
+//   FP64 beyond: 64 x 16 while the blocks all fit at once (512^2 6.68 / 10.0),
+//     then 32 x 16, two blocks per CU (2048^2 72.4 / 130).  At E10 the
+//     32 x 16 tile's 90 KB allow one block: 32 x 32, except between 2^19 and
+//     1.5 million nodes, where the state sits in the last-level cache and
+//     the one-step tile32x8r1 is ahead (1001 x 777: 20.5, against 24.8 for
+//     the best two-step shape).
+static int auto_variant_d2q9(const sc_lbm_params& p, int64_t n)
+{
+    constexpr int kOne = 2, k32x16 = 11, k64x16 = 13, k32x32 = 14, k32x8t1024 = 16;
+    const bool e10 = p.order == 10;
+    if (n < 110000) return k32x8t1024;
+    if (p.precision != SC_FP64) return e10 ? k32x32 : k64x16;
+    if (n < (int64_t)1 << 19) return e10 ? k32x32 : k64x16;
+    if (!e10) return k32x16;
+    return n < 1500000 ? kOne : k32x32;
+}
+
+// Any-lattice 2D kernels (P-R psi, EDM): the two-step tiles wherever the
+// largest that fits in LDS keeps its waves busy; us per step against the
+// one-step shapes taken before (wide32x8r1 below 2^20 nodes, wide128x16r2 or,
+// D2Q25 in FP64, wide64x8r2 from there).
+//   FP32, below 2^17 nodes: 64 x 8 with 1024 threads, latency counts (256^2:
+//     D2Q9 E8 3.12, D2Q13 E6 3.83 / 5.22, D2Q25 E8 5.46 / 6.71);
+//   FP32 up to 2^19: 64 x 16 with 1024 threads (512^2: D2Q25 E8 9.5 / 13.6),
+//     except D2Q25 E10, which it does not fit;
+//   FP32 beyond: the tile with the smallest halo share among those measured
+//     per lattice and order (4096 x 3000: D2Q13 E6 64 x 12 166, D2Q25 E8 64 x 16
+//     388 / 535); D2Q13 E10 and D2Q25 from E6 run one step at a time between
+//     2^19 and 1.5 million nodes, where the state sits in the last-level cache
+//     (1001 x 777 D2Q25 E8: 31.1, two steps 34.7);
+//   FP64: as FP32 with the tiles that still fit; D2Q25 from E6 only fits 32 x 4
+//     and runs one step (4096 x 3000 E8: 1068, two steps 1336), as D2Q13 does in
+//     the cached range.
+static int auto_variant_wide(const sc_lbm_params& p, int64_t n)
+{
+    constexpr int k64x8r2 = 0, k32x8r1 = 1, k64x16r2 = 3, k128x16r2 = 4;                             // one step
+    constexpr int t32x8 = 6, t64x8 = 7, t64x16t1024 = 8, t64x8t1024 = 10, t64x12t768 = 11;           // two steps
+    const int E = p.order;
+    const bool cached = n < 1500000;   // from 2^19 nodes
+    if (p.precision != SC_FP64) {
+        if (n < (int64_t)1 << 17) return t64x8t1024;
+        if (p.lattice == SC_D2Q25) {
+            if (n < (int64_t)1 << 19) return E == 10 ? t64x8t1024 : t64x16t1024;
+            if (E == 4) return t64x8;
+            if (cached) return k128x16r2;
+            return E == 10 ? t64x12t768 : t64x16t1024;
+        }
+        if (n < (int64_t)1 << 19) return t64x16t1024;
+        if (p.lattice == SC_D2Q9) return E == 10 ? t64x12t768 : t64x16t1024;
+        if (E == 10) return cached ? k128x16r2 : t64x8;
+        return E == 4 ? t64x16t1024 : t64x12t768;
+    }
+    if (p.lattice == SC_D2Q25) {
+        if (E == 4) return t32x8;
+        if (n < (int64_t)1 << 17) return k32x8r1;
+        return n < (int64_t)1 << 19 ? k64x16r2 : k64x8r2;
+    }
+    if (n < (int64_t)1 << 17) return t64x8t1024;
+    if (p.lattice == SC_D2Q9) {
+        if (n < (int64_t)1 << 19) return t64x16t1024;
+        if (E == 4) return t32x8;
+        return E == 10 ? (cached ? k32x8r1 : t32x8) : t64x8;
+    }
+    if (n < (int64_t)1 << 19) return E == 4 ? t64x16t1024 : (E == 10 ? k64x16r2 : t64x8t1024);
+    if (E == 4) return t32x8;
+    return cached ? k128x16r2 : t64x12t768;
+}
+
 // D3Q19: the persistent march with balanced segments, on 64 x 8 tiles in
 // FP32 and 32 x 8 in FP64.  Its segment height follows the grid, so one shape
 // serves every size.  ms per step, MRT E8, against the one-segment shapes
@@ -401,13 +478,9 @@ static int auto_variant(const sc_lbm_params& p, int64_t n)
     const int tuned = tune_lookup(p);
     if (tuned >= 0) return tuned;
     switch (family_of(p)) {
-    case kFamD2Q9: return n < (int64_t)1 << 20 ? 2 : 0;   // tile32x8r1 / tile64x16r4
+    case kFamD2Q9: return auto_variant_d2q9(p, n);
     case kFamD3Q19: return auto_variant_3d(p);
-    default:
-        if (n < (int64_t)1 << 20) return 1;                    // wide32x8r1
-        // wide128x16r2; its 1024-thread blocks spill the FP64 D2Q25 step, which
-        // takes wide64x8r2 (512 threads)
-        return (p.precision == SC_FP64 && p.lattice == SC_D2Q25) ? 0 : 4;
+    default: return auto_variant_wide(p, n);
     }
 }
 
@@ -649,8 +722,9 @@ extern "C" void* sc_lbm_stream(sc_lbm* h) { return h ? (void*)h->stream : nullpt
 extern "C" double sc_lbm_rho_ref(const sc_lbm* h) { return h ? h->p.rho_ref : std::nan(""); }
 
 
-// single-step D2Q9 shape used for the odd step of a two-step shape
-constexpr int kSingleStepD2Q9 = 2;   // tile32x8r1
+// single-step D2Q9 shape used for the odd step of a two-step shape:
+// tile32x8r1, or tile64x16r4 on large grids (2048^2 E8 FP32: 76 us against 93)
+static int single_step_d2q9(int64_t n) { return n < ((int64_t)1 << 20) ? 2 : 0; }
 
 template <typename T>
 static hipError_t launch_family(sc_lbm* h, const StepArgs<T>& a, bool single = false)
@@ -658,8 +732,8 @@ static hipError_t launch_family(sc_lbm* h, const StepArgs<T>& a, bool single = f
     const sc_lbm_params& p = h->p;
     switch (handle_family(h)) {
     case kFamD2Q9:
-        return launch_step_d2q9(a, p.order, single && variant_steps_d2q9(h->variant) != 1 ? kSingleStepD2Q9 : h->variant,
-                                h->stream);
+        return launch_step_d2q9(
+            a, p.order, single && variant_steps_d2q9(h->variant) != 1 ? single_step_d2q9(h->n) : h->variant, h->stream);
     case kFamD3Q19: return launch_step_d3q19(a, p.order, p.collision == SC_MRT, h->variant, h->stream);
     default: {
         // the odd step of a two-step shape, and every step with walls, take a

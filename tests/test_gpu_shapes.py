@@ -47,3 +47,17 @@ def test_balanced_march(shape, order, collision, prec):
     n = B.sc_lbm_num_variants(B.make_params("D3Q19", shape))
     for v in (-1, n - 2, n - 1):
         _agree(rho0, "D3Q19", 6, prec, v, 2, order=order, collision=collision, tau=0.9)
+
+
+# sizes on either side of each line of the 2D rule; 5 steps: two two-step
+# launches and the single step of the remainder
+@pytest.mark.parametrize("shape", [(60, 40), (331, 332), (410, 390), (1030, 520), (1300, 1160)])
+@pytest.mark.parametrize("lattice", ["D2Q9", "D2Q9edm", "D2Q13", "D2Q25"])
+@pytest.mark.parametrize("order", [4, 8, 10])
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+def test_automatic_2d_shape(shape, lattice, order, prec):
+    """The automatic 2D shape against a one-step shape of the same family
+    (tile64x8r2 / wide32x8r1)."""
+    rho0 = droplet_rho(shape, 13, seed=5)
+    edm = lattice != "D2Q9"
+    _agree(rho0, lattice.replace("edm", ""), 5, prec, -1, 1, order=order, tau=0.9, forcing="edm" if edm else "guo")
