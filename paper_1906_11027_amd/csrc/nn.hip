@@ -394,166 +394,304 @@ k_conv_bwd_w(const float* __restrict__ in, const float* __restrict__ gout, float
 // pixels, gW_t[co][ci] += g[co][p] x[ci][p + d_t], with both operands split
 // exactly into three bf16 parts and the six part products whose weights
 // reach 2^-24 summed (hi.hi, hi.mid, mid.hi, hi.lo, mid.mid, lo.hi): FP32
-// operands to within about 2^-24 of each product.  k runs over 32 pixels
-// (two tile rows) per MFMA, 8 consecutive pixels of one row per lane.  A tap
-// shifts the input by dx = 0, 1, 2 columns, so its 8-pixel run is 16-byte
-// aligned (one vector read), 4-byte aligned (four dword reads) or 2-byte
-// aligned (five dword reads realigned by v_alignbyte).  LDS: the input tile
-// with its halo as [part][ci][18 rows][24 columns] and the output gradient as
-// [part][co][256 + 8]; channel strides of 220 and 132 dwords put the 16
-// channels a quarter-wave reads on distinct bank quads.  One block per CU
-// (135 KB of LDS); wave v owns the 16 x 16 block (co tile v / 2, ci tile
-// v % 2) of all nine taps.  The bias gradient sums the FP32 output gradient
-// per thread and channel, then over the block in a fixed order.
-constexpr int kXRS = 24;                       // bf16 per input row in LDS (18 + pad, 16-byte rows)
-constexpr int kXCS = 18 * kXRS + 8;            // bf16 per input channel (220 dwords = 28 mod 64)
-constexpr int kXPart = MAXC * kXCS;
-constexpr int kGCS = TS * TS + 8;              // bf16 per output-gradient channel (132 dwords = 4 mod 64)
-constexpr int kGPart = MAXC * kGCS;
+// operands to within about 2^-24 of each product.
+//
+// Partial row v sums the 16 x 16 tiles xcd_swizzle(v) + k nblk, k = 0, 1, ...,
+// eight chunks of two tile rows (32 pixels, one MFMA's k) per tile.  A group
+// of four waves, one per 16 x 16 (co, ci) block of all nine taps, works on one
+// row; two groups share a block.  The waves run independently: each stages its
+// own 16 input and 16 gradient channels, two image rows at a time, through an
+// LDS patch of its own (FP32; 4 lanes load a channel row's 64 bytes, the patch
+// turns them into the operands' layout, 8 consecutive pixels of one channel
+// per lane) and splits them in registers.  No barrier in the loop.
+//
+// With pairs P_s = input rows (y0 - 1 + 2s, y0 + 2s), s = 0 .. 8, and M_s = the
+// second row of P_(s-1) with the first of P_s, chunk c multiplies its gradient
+// rows with P_c (dy = -1), M_(c+1) (dy = 0) and P_(c+1) (dy = +1).  The three
+// column shifts of an operand are the same ten split values packed in pairs
+// from three starts.  Software pipeline, per pair: pass the loaded rows through
+// the patch, issue the next loads, then the products of the chunk before run
+// beside the splits of this one.
+//
+// One barrier per tile keeps a block's waves on the same tiles: without it they
+// drift apart and fetch each line twice (553 against 276 MB at batch 16,
+// 256 x 256).
+//
+// What bounds it: vector issue and the matrix cores, 224 VALU instructions
+// beside 54 MFMAs per step and wave.  At batch 16, 256 x 256 it takes 147 us,
+// where staging the parts of a whole tile through block-wide LDS took 223 (16-bit
+// stores, one block per CU).  Every accumulator sums the same products in the
+// same order as that kernel did, so the gradients are the same to the bit.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
-template <int DX>
-__device__ __forceinline__ bf16x8 x_run(const uint16_t* __restrict__ xs, int e)
+// packed bf16 pairs (high halves) of two FP32 bit patterns: a in the low half
+__device__ __forceinline__ uint32_t pack_hi(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
+
+// the three bf16 parts of v as FP32 bit patterns whose top halves are the parts
+__device__ __forceinline__ void split3_bits(float v, uint32_t& u0, uint32_t& u1, uint32_t& u2)
 {
-    if (DX == 0) return *(const bf16x8*)(xs + e);
-    u32x4 v;
-    if (DX == 2) {
-        const uint32_t* d = (const uint32_t*)(xs + e);
-        v = u32x4{d[0], d[1], d[2], d[3]};
-    } else {
-        const uint32_t* d = (const uint32_t*)(xs + e - 1);
-        const uint32_t d0 = d[0], d1 = d[1], d2 = d[2], d3 = d[3], d4 = d[4];
-        v = u32x4{__builtin_amdgcn_alignbyte(d1, d0, 2), __builtin_amdgcn_alignbyte(d2, d1, 2),
-                  __builtin_amdgcn_alignbyte(d3, d2, 2), __builtin_amdgcn_alignbyte(d4, d3, 2)};
-    }
-    return __builtin_bit_cast(bf16x8, v);
+    u0 = __float_as_uint(v);
+    const float r1 = v - __uint_as_float(u0 & 0xffff0000u);
+    u1 = __float_as_uint(r1);
+    u2 = __float_as_uint(r1 - __uint_as_float(u1 & 0xffff0000u));
 }
 
-__global__ void __launch_bounds__(TS* TS, 1)
-k_conv_bwd_w_bf16(const float* __restrict__ in, const float* __restrict__ gout, float* __restrict__ partial,
-                  int batch, int h, int wd)
+// v with xcd_swizzle(v, nb) == L
+__device__ __forceinline__ int xcd_unswizzle(int L, int nb)
 {
-    __shared__ __align__(16) uint16_t xs[3 * kXPart];
-    __shared__ __align__(16) uint16_t gs[3 * kGPart];
-    const int tid = threadIdx.y * TS + threadIdx.x;
-    const int lane = tid & 63, wv = tid >> 6;
-    const int mt = wv >> 1, nt = wv & 1;
-    const int r16 = lane & 15, kq = lane >> 4;
-    const int tiles_x = (wd + TS - 1) / TS, tiles_y = (h + TS - 1) / TS;
-    const int nwork = tiles_x * tiles_y * batch;
-    const int64_t plane = (int64_t)h * wd;
+    const int q = nb >> 3, r = nb & 7;
+    if (L < r * (q + 1)) return (L % (q + 1)) * 8 + L / (q + 1);
+    const int m = L - r * (q + 1);
+    return (m % q) * 8 + r + m / q;
+}
+
+constexpr int kWGroups = 2;                    // partial rows a block works on
+constexpr int kWXRow = 24;                     // floats per input channel row: pixel p at 4 + p, outer pixels at 3 and 20
+constexpr int kWGRow = 20;                     // floats per gradient channel row
+constexpr int kWPatch = 4 * 16 * kWXRow + 2 * 16 * kWGRow;   // floats of a wave: two input pairs, one gradient pair
+
+// RAGGED: the image width is not a multiple of 16, columns are loaded one by
+// one, wrapped
+template <bool RAGGED>
+__global__ void __launch_bounds__(256 * kWGroups)
+k_conv_bwd_w_bf16(const float* __restrict__ in, const float* __restrict__ gout, float* __restrict__ partial,
+                  int nblk, int batch, int h, int wd)
+{
     constexpr int E = MAXC * MAXC * 9;
+    constexpr int RED = kWGroups * E > 4 * kWGroups * kWPatch ? kWGroups * E : 4 * kWGroups * kWPatch;
+    __shared__ __align__(16) float lds[RED];
+    __shared__ float redb[kWGroups * MAXC];
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int grp = wv >> 2, mt = (wv >> 1) & 1, nt = wv & 1;
+    const int r16 = lane & 15, kq = lane >> 4, rs = kq >> 1, c8 = 8 * (kq & 1);
+    const int L0 = xcd_swizzle(blockIdx.x, gridDim.x) * kWGroups + grp;   // this group's first tile
+    const bool active = L0 < nblk;
+    const int tiles_x = (wd + TS - 1) / TS, tiles = tiles_x * ((h + TS - 1) / TS);
+    const int nwork = tiles * batch;
+    const int wend = nwork + grp;   // the block's groups take equally many tiles
+    const int64_t plane = (int64_t)h * wd;
+    float* xpatch = lds + wv * kWPatch;
+    float* gpatch = xpatch + 4 * 16 * kWXRow;
+
     f32x4 acc[9];
 #pragma unroll
     for (int t = 0; t < 9; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float bsum[MAXC];
-#pragma unroll
-    for (int c = 0; c < MAXC; ++c) bsum[c] = 0.f;
-    const bool two = tid + TS * TS < kHaloPx;
-    const int r1 = two ? tid + TS * TS : 0;
-    // the tile's loads for the next work item are issued before this one's
-    // products, so their latency hides behind the MFMAs (one block per CU)
-    float gv[MAXC], xv[MAXC], xw[MAXC];
-    auto load = [&](int wi) {
-        const int b = wi / (tiles_x * tiles_y), tt = wi % (tiles_x * tiles_y);
+    float bsum = 0.f;
+
+    // loading lane: 4 pixels from 4 (lane & 3) of channel lane / 4; outer
+    // pixels: channel lane & 15 of row (lane / 16) & 1, left or right by lane / 32
+    struct Raw {
+        f32x4 x[2], g[2];
+        float o;
+    };
+    struct Place {   // where a step's rows lie (uniform)
+        int wi, s;
+    };
+    auto load = [&](const Place& at, Raw& v) {
+        const int wi = at.wi < nwork ? at.wi : nwork - 1;
+        const int b = wi / tiles, tt = wi - b * tiles;
         const int x0 = (tt % tiles_x) * TS, y0 = (tt / tiles_x) * TS;
-        const float* gb = gout + (int64_t)b * MAXC * plane;
-        const float* xb0 = in + (int64_t)b * MAXC * plane;
-        const int x = x0 + tid % TS, y = y0 + tid / TS;
-        const bool in_img = x < wd && y < h;
-        const uint32_t po = (uint32_t)(y * wd + x);
-        const uint32_t h0 = (uint32_t)(wrapc(y0 + tid / (TS + 2) - 1, h) * wd + wrapc(x0 + tid % (TS + 2) - 1, wd));
-        const uint32_t h1 = (uint32_t)(wrapc(y0 + r1 / (TS + 2) - 1, h) * wd + wrapc(x0 + r1 % (TS + 2) - 1, wd));
+        const float* xb = in + ((int64_t)b * MAXC + nt * 16) * plane;
+        const float* gb = gout + ((int64_t)b * MAXC + mt * 16) * plane;
+        const int64_t cl = (int64_t)(lane >> 2) * plane;
+        int xc[4];
 #pragma unroll
-        for (int c = 0; c < MAXC; ++c) {
-            const uint32_t co = (uint32_t)c * (uint32_t)plane;
-            gv[c] = in_img ? gb[co + po] : 0.f;
-            xv[c] = xb0[co + h0];
-            xw[c] = two ? xb0[co + h1] : 0.f;
+        for (int j = 0; j < 4; ++j) xc[j] = RAGGED ? wrapc(x0 + 4 * (lane & 3) + j, wd) : x0 + 4 * (lane & 3) + j;
+        int64_t xr[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            xr[i] = (int64_t)wrapc(y0 - 1 + 2 * at.s + i, h) * wd;
+            const int gy = y0 + 2 * at.s - 2 + i;   // s = 0 has no chunk: its gradient is dropped
+            const int64_t gr = (int64_t)(gy < 0 ? 0 : (gy < h ? gy : h - 1)) * wd;
+            if (RAGGED) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    v.x[i][j] = xb[cl + xr[i] + xc[j]];
+                    v.g[i][j] = gb[cl + gr + xc[j]];
+                }
+            } else {
+                v.x[i] = *(const f32x4u*)(xb + cl + xr[i] + xc[0]);
+                v.g[i] = *(const f32x4u*)(gb + cl + gr + xc[0]);
+            }
+        }
+        v.o = xb[(int64_t)r16 * plane + (lane & 16 ? xr[1] : xr[0]) + wrapc(lane & 32 ? x0 + TS : x0 - 1, wd)];
+    };
+    // pair slot: 16 channels of two rows
+    auto stage = [&](const Raw& v, int slot) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            *(f32x4*)(xpatch + ((2 * slot + i) * 16 + (lane >> 2)) * kWXRow + 4 + 4 * (lane & 3)) = v.x[i];
+            *(f32x4*)(gpatch + (i * 16 + (lane >> 2)) * kWGRow + 4 * (lane & 3)) = v.g[i];
+        }
+        xpatch[((2 * slot + ((lane >> 4) & 1)) * 16 + r16) * kWXRow + (lane & 32 ? 20 : 3)] = v.o;
+    };
+    auto take_g = [&](float (&d)[8]) {
+        const float* g = gpatch + (rs * 16 + r16) * kWGRow + c8;
+        const f32x4 g0 = *(const f32x4*)g, g1 = *(const f32x4*)(g + 4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            d[j] = g0[j];
+            d[4 + j] = g1[j];
         }
     };
-    int wi = xcd_swizzle(blockIdx.x, gridDim.x);
-    if (wi < nwork) load(wi);
-    for (; wi < nwork; wi += gridDim.x) {
-        __syncthreads();   // the previous item's reads of gs and xs are done
-        {
-            const int ly0 = tid / (TS + 2), lx0 = tid % (TS + 2);
-            const int ly1 = r1 / (TS + 2), lx1 = r1 % (TS + 2);
+    // rows (a, b) for the lanes of the first and the second row; row k of slot
+    // s is 2 s + k
+    auto take_x = [&](int a, int b, float (&d)[10]) {
+        const float* p = xpatch + ((rs ? b : a) * 16 + r16) * kWXRow + 4 + c8;
+        const f32x4 p0 = *(const f32x4*)p, p1 = *(const f32x4*)(p + 4);
+        d[0] = p[-1];
+        d[9] = p[8];
 #pragma unroll
-            for (int c = 0; c < MAXC; ++c) {
-                bsum[c] += gv[c];
-                uint32_t p0, p1, p2;
-                split3(gv[c], p0, p1, p2);
-                uint16_t* gd = gs + c * kGCS + tid;
-                gd[0] = (uint16_t)p0;
-                gd[kGPart] = (uint16_t)p1;
-                gd[2 * kGPart] = (uint16_t)p2;
-                split3(xv[c], p0, p1, p2);
-                uint16_t* xd = xs + c * kXCS + ly0 * kXRS + lx0;
-                xd[0] = (uint16_t)p0;
-                xd[kXPart] = (uint16_t)p1;
-                xd[2 * kXPart] = (uint16_t)p2;
-                if (two) {
-                    split3(xw[c], p0, p1, p2);
-                    uint16_t* xe = xs + c * kXCS + ly1 * kXRS + lx1;
-                    xe[0] = (uint16_t)p0;
-                    xe[kXPart] = (uint16_t)p1;
-                    xe[2 * kXPart] = (uint16_t)p2;
-                }
-            }
+        for (int j = 0; j < 4; ++j) {
+            d[1 + j] = p0[j];
+            d[5 + j] = p1[j];
         }
-        __syncthreads();
-        if (wi + (int)gridDim.x < nwork) load(wi + gridDim.x);
-        const uint16_t* ga = gs + (mt * 16 + r16) * kGCS;
-        const int xb = (nt * 16 + r16) * kXCS;
+    };
+    // one part of an operand: pairs from pixel -1 (five) and from pixel 0 (four)
+    struct Part {
+        u32x4 ev, od;
+        uint32_t el;
+    };
+    auto split_x = [&](const float (&v)[10], Part (&d)[3]) {
+        uint32_t t[3][10];
+#pragma unroll
+        for (int j = 0; j < 10; ++j) split3_bits(v[j], t[0][j], t[1][j], t[2][j]);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            d[k].ev = u32x4{pack_hi(t[k][0], t[k][1]), pack_hi(t[k][2], t[k][3]), pack_hi(t[k][4], t[k][5]),
+                            pack_hi(t[k][6], t[k][7])};
+            d[k].od = u32x4{pack_hi(t[k][1], t[k][2]), pack_hi(t[k][3], t[k][4]), pack_hi(t[k][5], t[k][6]),
+                            pack_hi(t[k][7], t[k][8])};
+            d[k].el = pack_hi(t[k][8], t[k][9]);
+        }
+    };
+    // gradient outside the image and of s = 0 enters as zero
+    auto split_g = [&](const float (&v)[8], const Place& at, u32x4 (&d)[3]) {
+        const int tt = at.wi % tiles;
+        const int left = RAGGED ? wd - (tt % tiles_x) * TS - c8 : 8;   // columns inside the image
+        const bool row = at.s > 0 && at.wi < nwork && active && (tt / tiles_x) * TS + 2 * at.s - 2 + rs < h;
+        uint32_t t[3][8];
+        float m[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            m[j] = row && (!RAGGED || j < left) ? v[j] : 0.f;
+            split3_bits(m[j], t[0][j], t[1][j], t[2][j]);
+        }
+        bsum += ((m[0] + m[1]) + (m[2] + m[3])) + ((m[4] + m[5]) + (m[6] + m[7]));
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            d[k] = u32x4{pack_hi(t[k][0], t[k][1]), pack_hi(t[k][2], t[k][3]), pack_hi(t[k][4], t[k][5]),
+                         pack_hi(t[k][6], t[k][7])};
+    };
+
+    Part P[2][3], M[3];
+    u32x4 G[2][3];
+    auto products = [&](const Part (&x)[3], const u32x4 (&g)[3], int dy) {
+#pragma unroll
+        for (int xp = 0; xp < 3; ++xp) {
+            const u32x4 e = x[xp].ev;
+            const u32x4 v[3] = {e, x[xp].od, u32x4{e[1], e[2], e[3], x[xp].el}};
+#pragma unroll
+            for (int gp = 0; gp + xp < 3; ++gp)
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx)
+                    acc[3 * dy + dx] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, g[gp]),
+                                                                               __builtin_bit_cast(bf16x8, v[dx]),
+                                                                               acc[3 * dy + dx], 0, 0, 0);
+        }
+    };
+    auto mix = [] {   // one MFMA to a few VALU instructions
+#pragma unroll
+        for (int k = 0; k < 18; ++k) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    // every wave of the block takes the same number of tiles, so that the
+    // barrier below is met by all; a group without a tile works on the last
+    // one with zero gradients
+    if (nwork > 0) {
+        Raw raw;
+        float gv[8], xv[10], mv[10];
+        load(Place{L0, 0}, raw);
+        stage(raw, 0);
+        load(Place{L0, 1}, raw);
+        take_x(0, 1, xv);
+        split_x(xv, P[0]);
+        for (int wi = L0; wi < wend; wi += nblk) {
+            __builtin_amdgcn_s_barrier();
+            // P[0] = P_0 of this tile.  Step s = 1 has no chunk before it.
+            stage(raw, 1);
+            take_g(gv);
+            take_x(2, 3, xv);
+            take_x(1, 2, mv);
+            load(Place{wi, 2}, raw);
+            split_g(gv, Place{wi, 1}, G[1]);
+            split_x(xv, P[1]);
+            split_x(mv, M);
+            // step s, pair slot s & 1: the products of chunk s - 2 beside the splits of chunk s - 1
+            auto step = [&](int slot, int s, const Place& ahead) {
+                stage(raw, slot);
+                take_g(gv);
+                load(ahead, raw);
+                __builtin_amdgcn_sched_barrier(0);
+                take_x(2 * slot, 2 * slot + 1, xv);
+                products(P[slot], G[slot ^ 1], 0);
+                split_g(gv, Place{wi, s}, G[slot]);
+                mix();
+                take_x(2 * (slot ^ 1) + 1, 2 * slot, mv);
+                products(M, G[slot ^ 1], 1);
+                split_x(xv, P[slot]);
+                mix();
+                products(P[slot ^ 1], G[slot ^ 1], 2);
+                split_x(mv, M);
+                mix();
+            };
 #pragma unroll 1
-        for (int ch = 0; ch < TS * TS / 32; ++ch) {
-            const int p0 = 32 * ch + 8 * kq;           // this lane's 8 pixels
-            const int ry = p0 / TS, cx0 = p0 % TS;     // tile row, first column
-            bf16x8 a[3];
-#pragma unroll
-            for (int gp = 0; gp < 3; ++gp) a[gp] = *(const bf16x8*)(ga + gp * kGPart + p0);
-#pragma unroll
-            for (int t = 0; t < 9; ++t) {
-                const int dy = t / 3, dx = t % 3;
-                const int e = xb + (ry + dy) * kXRS + cx0 + dx;
-#pragma unroll
-                for (int xp = 0; xp < 3; ++xp) {
-                    const int ex = e + xp * kXPart;
-                    const bf16x8 bv = dx == 0 ? x_run<0>(xs, ex) : (dx == 1 ? x_run<1>(xs, ex) : x_run<2>(xs, ex));
-#pragma unroll
-                    for (int gp = 0; gp + xp < 3; ++gp)
-                        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[gp], bv, acc[t], 0, 0, 0);
-                }
+            for (int s = 2; s < 8; s += 2) {
+                step(0, s, Place{wi, s + 1});
+                step(1, s + 1, Place{wi, s + 2});
             }
+            step(0, 8, Place{wi + nblk, 0});
+            // the last chunk beside the next tile's first pair
+            stage(raw, 0);
+            load(Place{wi + nblk, 1}, raw);
+            __builtin_amdgcn_sched_barrier(0);
+            take_x(0, 1, xv);
+            products(P[1], G[0], 0);
+            products(M, G[0], 1);
+            products(P[0], G[0], 2);
+            split_x(xv, P[0]);
         }
     }
-    float* pb = partial + (int64_t)blockIdx.x * (E + MAXC);
-    const int ci = nt * 16 + r16;
+    __syncthreads();   // every wave is done with its patch
+
+    float* red = lds + grp * E;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int co = mt * 16 + 4 * kq + i;
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int t = 0; t < 9; ++t) pb[(ci * MAXC + co) * 9 + t] = acc[t][i];
-    }
-    // bias: each thread's per-channel sums, then over the block in a fixed
-    // order (thread 0, 1, ...) through LDS
+        for (int t = 0; t < 9; ++t) red[((nt * 16 + r16) * MAXC + mt * 16 + 4 * kq + i) * 9 + t] = acc[t][i];
+    // bias: the four pixel octets of a channel
+    bsum += __shfl_xor(bsum, 16, 64);
+    bsum += __shfl_xor(bsum, 32, 64);
+    if (nt == 0 && kq == 0) redb[grp * MAXC + mt * 16 + r16] = bsum;
     __syncthreads();
-    float* red = (float*)xs;   // MAXC x 256 floats fit in the input tile's LDS
-#pragma unroll
-    for (int c = 0; c < MAXC; ++c) red[c * (TS * TS) + tid] = bsum[c];
-    __syncthreads();
-    if (tid < MAXC) {
-        float sb = 0.f;
-        for (int k = 0; k < TS * TS; ++k) sb += red[tid * (TS * TS) + k];
-        pb[E + tid] = sb;
-    }
+    if (!active) return;
+    float* pb = partial + (int64_t)xcd_unswizzle(L0, nblk) * (E + MAXC);
+    const int t4 = threadIdx.x & 255;
+    for (int e = t4; e < E; e += 256) pb[e] = red[e];
+    if (t4 < MAXC) pb[E + t4] = redb[grp * MAXC + t4];
 }
 
 // Sum the per-block partials in a fixed order: gw[co][ci][k] from the
 // ci-major partial entries, gbias[co] from the trailing bias columns.  A block
 // covers 64 columns with 4 row groups (rows r = g mod 4), combined in group
-// order through LDS.
+// order through LDS.  A thread's additions are a chain; its loads run ahead of
+// it (512 rows of 9,248 columns: 6.4 us, 20 with one load at a time).
 constexpr int kSumCols = 64, kSumGroups = 4;
 __global__ void __launch_bounds__(kSumCols* kSumGroups)
 k_sum_partials(const float* __restrict__ m, int nrow, int cin, int cout, float* __restrict__ gw,
@@ -565,8 +703,18 @@ k_sum_partials(const float* __restrict__ m, int nrow, int cin, int cout, float* 
     const int lc = threadIdx.x % kSumCols, g = threadIdx.x / kSumCols;
     const int j = blockIdx.x * kSumCols + lc;
     float s = 0.f;
-    if (j < ncol)
-        for (int r = g; r < nrow; r += kSumGroups) s += m[(int64_t)r * ncol + j];
+    if (j < ncol) {
+        // sixteen loads in flight; the additions keep their order
+        int r = g;
+        for (; r + 15 * kSumGroups < nrow; r += 16 * kSumGroups) {
+            float v[16];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) v[k] = m[(int64_t)(r + k * kSumGroups) * ncol + j];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) s += v[k];
+        }
+        for (; r < nrow; r += kSumGroups) s += m[(int64_t)r * ncol + j];
+    }
     part[g][lc] = s;
     __syncthreads();
     if (g != 0 || j >= ncol) return;
@@ -815,7 +963,12 @@ extern "C" int sc_nn_conv3x3_bwd_weight(const float* in, const float* gout, floa
     const int E = cin * cout * 9;
     hipStream_t s = (hipStream_t)stream;
     if (cin == MAXC && cout == MAXC)
-        hipLaunchKernelGGL(k_conv_bwd_w_bf16, nblk, dim3(TS, TS), 0, s, in, gout, partial_scratch, batch, h, wd);
+        if (wd % TS)
+            hipLaunchKernelGGL(k_conv_bwd_w_bf16<true>, (nblk + kWGroups - 1) / kWGroups, 256 * kWGroups, 0, s, in, gout,
+                               partial_scratch, nblk, batch, h, wd);
+        else
+            hipLaunchKernelGGL(k_conv_bwd_w_bf16<false>, (nblk + kWGroups - 1) / kWGroups, 256 * kWGroups, 0, s, in, gout,
+                               partial_scratch, nblk, batch, h, wd);
     else
         hipLaunchKernelGGL(k_conv_bwd_w, nblk, dim3(TS, TS), 0, s, in, gout, partial_scratch, batch, cin, cout, h,
                            wd);
