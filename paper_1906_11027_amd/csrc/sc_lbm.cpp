@@ -376,81 +376,132 @@ static void tune_store(const sc_lbm_params& p, int variant, double ms)
     std::fclose(f);
 }
 
+// tiles of tx x ty nodes over the grid, and how much wider than the grid the
+// tile columns are
+static int64_t tiles_of(const sc_lbm_params& p, int tx, int ty)
+{
+    return (int64_t)((p.nx + tx - 1) / tx) * ((p.ny + ty - 1) / ty);
+}
+static double overhang(const sc_lbm_params& p, int tx) { return (double)((p.nx + tx - 1) / tx * tx) / p.nx; }
+
 // D2Q9 with Guo forcing: the two-step tiles, which read and write the state
 // once per two steps and halve the launches.  us per step, E8 unless marked,
 // against the one-step shapes that were taken before (tile32x8r1 below 2^20
-// nodes, tile64x16r4 from there):
-//   up to about 330^2 the grid has few tiles per CU and latency counts: 32 x 8
-//     tiles with 1024 threads (256^2: FP32 2.57 / 3.64, FP64 3.34 / 4.62);
-//   FP32 beyond: 64 x 16, the smallest halo share (512^2 3.84 / 6.35, 2048^2
-//     43.7 / 78.3, 8192^2 638 / 1120).  At E10 its LDS leaves one block per CU
-//     and 32 x 32 is ahead (2048^2 48.9 / 63.5 for 64 x 16);
-//   FP64 beyond: 64 x 16 while the blocks all fit at once (512^2 6.68 / 10.0),
-//     then 32 x 16, two blocks per CU (2048^2 72.4 / 130).  At E10 the
-//     32 x 16 tile's 90 KB allow one block: 32 x 32, except between 2^19 and
-//     1.5 million nodes, where the state sits in the last-level cache and
-//     the one-step tile32x8r1 is ahead (1001 x 777: 20.5, against 24.8 for
-//     the best two-step shape).
+// nodes, tile64x16r4 from there).  The smallest tile that covers the grid with
+// one block per CU (256) is taken, since a second round of blocks costs as
+// much as the first:
+//   32 x 8 tiles with 1024 threads (256^2: FP32 2.57 / 3.64, FP64 3.34 / 4.62);
+//   32 x 16 (964 x 120: FP32 3.36 / 4.63, 32 x 8 in two rounds 3.9);
+//   64 x 16 (512^2: FP32 3.84 / 6.35, FP64 6.68 / 10.0), at E10 32 x 32.
+// Beyond, FP32 takes 64 x 16, the smallest halo share (2048^2 43.7 / 78.3, 8192^2
+// 638 / 1120); at E10 its LDS leaves one block per CU and 32 x 32 is ahead
+// (2048^2 48.9 / 63.5 for 64 x 16), except from 2^20 to 3 million nodes, where the
+// state half fits the last-level cache (1448^2: tile64x4r1 25.7, 32 x 32 28.3).
+// FP64 takes 32 x 16, two blocks per CU (2048^2
+// 72.4 / 130); at E10 the 32 x 16 tile's 90 KB allow one: 32 x 32, except below
+// 1.5 million nodes, where the state sits in the last-level cache and the one-step
+// tile32x8r1 is ahead (1001 x 777: 20.5, against 24.8 for the best two-step shape).
 static int auto_variant_d2q9(const sc_lbm_params& p, int64_t n)
 {
-    constexpr int kOne = 2, k32x16 = 11, k64x16 = 13, k32x32 = 14, k32x8t1024 = 16;
-    const bool e10 = p.order == 10;
-    if (n < 110000) return k32x8t1024;
-    if (p.precision != SC_FP64) return e10 ? k32x32 : k64x16;
-    if (n < (int64_t)1 << 19) return e10 ? k32x32 : k64x16;
-    if (!e10) return k32x16;
-    return n < 1500000 ? kOne : k32x32;
+    constexpr int kOne = 2, k64x4 = 3, k32x16 = 11, k64x16 = 13, k32x32 = 14, k32x8t1024 = 16;
+    const bool e10 = p.order == 10, cached = n >= (int64_t)1 << 20 && n < 3000000;
+    if (tiles_of(p, 32, 8) <= 256) return k32x8t1024;
+    if (tiles_of(p, 32, 16) <= 256) return k32x16;
+    if (p.precision != SC_FP64) return !e10 ? k64x16 : (cached ? k64x4 : k32x32);
+    if (e10) return tiles_of(p, 32, 32) <= 256 || n >= 1500000 ? k32x32 : kOne;
+    return tiles_of(p, 64, 16) <= 256 ? k64x16 : k32x16;
 }
 
-// Any-lattice 2D kernels (P-R psi, EDM): the two-step tiles wherever the
-// largest that fits in LDS keeps its waves busy; us per step against the
-// one-step shapes taken before (wide32x8r1 below 2^20 nodes, wide128x16r2 or,
-// D2Q25 in FP64, wide64x8r2 from there).
-//   FP32, below 2^17 nodes: 64 x 8 with 1024 threads, latency counts (256^2:
-//     D2Q9 E8 3.12, D2Q13 E6 3.83 / 5.22, D2Q25 E8 5.46 / 6.71);
-//   FP32 up to 2^19: 64 x 16 with 1024 threads (512^2: D2Q25 E8 9.5 / 13.6),
-//     except D2Q25 E10, which it does not fit;
-//   FP32 beyond: the tile with the smallest halo share among those measured
-//     per lattice and order (4096 x 3000: D2Q13 E6 64 x 12 166, D2Q25 E8 64 x 16
-//     388 / 535); D2Q13 E10 and D2Q25 from E6 run one step at a time between
-//     2^19 and 1.5 million nodes, where the state sits in the last-level cache
-//     (1001 x 777 D2Q25 E8: 31.1, two steps 34.7);
-//   FP64: as FP32 with the tiles that still fit; D2Q25 from E6 only fits 32 x 4
-//     and runs one step (4096 x 3000 E8: 1068, two steps 1336), as D2Q13 does in
-//     the cached range.
+// Two-step tiles 64 x 8, 64 x 12 and 64 x 16 (all of 768 or 1024 threads) on a
+// grid that a few rounds of blocks cover: a launch takes about rounds x the
+// nodes a tile pulls, (64 + 2 H)(TY + 2 H) with H = 2R + M, so the tile with
+// the least is taken (the smaller on a tie).  D2Q13 E8 659 x 238: 64 x 12, one
+// round, 5.1 us a step; 64 x 16 5.7, 64 x 8 in two rounds 6.1.  512^2 E6: 64 x 16,
+// one round, 5.6; 64 x 12 in two 6.8.  75 x 2662 E6: 64 x 12 6.3, 64 x 16 8.9.
+static int two_step_height(const sc_lbm_params& p, int reach)
+{
+    const int R = p.order == 4 ? 1 : (p.order == 10 ? 3 : 2), H = 2 * R + reach;
+    int best = 8;
+    int64_t least = INT64_MAX;
+    for (int ty = 8; ty <= 16; ty += 4) {
+        const int64_t tiles = tiles_of(p, 64, ty);
+        const int64_t cost = (tiles + 255) / 256 * (64 + 2 * H) * (ty + 2 * H);
+        if (cost < least) {
+            least = cost;
+            best = ty;
+        }
+    }
+    return best;
+}
+
+// Any-lattice 2D kernels (P-R psi, EDM); us per step against the one-step
+// shapes taken before (wide32x8r1 below 2^20 nodes, wide128x16r2 or, D2Q25 in
+// FP64, wide64x8r2 from there).
+//   FP32 below 2^19 nodes: the two-step tile of two_step_height (256^2: D2Q9 E8
+//     3.12, D2Q13 E6 3.83 / 5.22, D2Q25 E8 5.46 / 6.71; 512^2 D2Q25 E8 9.5 / 13.6);
+//     at E10, whose halos are the widest, 32 x 8 where 64-wide columns hang over
+//     by a fifth (96 x 2511 D2Q13: 8.6 / 9.0, 64 x 12 10.0), one step where even
+//     those take many rounds (143 x 2827: 12.8, two steps 15.3);
+//   FP32 beyond: the tile with the smallest halo share that still leaves two
+//     blocks per CU (4096 x 3000: D2Q13 E6 64 x 12 166, D2Q25 E8 64 x 16 388 /
+//     535).  While the state sits in the last-level cache, D2Q25 from E6 (below
+//     1.5 million nodes) and D2Q13 E10 (3 million) run one step at a time: the
+//     halo collisions cost more than the pass saved (1001 x 777 D2Q25 E8: 31.1,
+//     two steps 34.7; 1151 x 2081 D2Q13 E10: 44.6, two steps 54.4);
+//   FP64, D2Q9: as FP32 with the tiles that still fit;
+//   FP64, D2Q13: 64 x 8 or 64 x 12 while two rounds cover the grid (256^2 E6 5.6 /
+//     6.4; 832 x 215 E8 64 x 12 7.9 / 10.5; three rounds of 64 x 8, 220 x 1452:
+//     15.7, one step 14.0) and two steps again from 2^20 nodes (2623 x 508 E8: 54.1 / 55.4; 4096 x 3000 E6: 404 / 533);
+//   FP64, D2Q25: from E6 only 32 x 4 fits, one step is ahead (4096 x 3000 E8:
+//     1068, two steps 1336).
 static int auto_variant_wide(const sc_lbm_params& p, int64_t n)
 {
     constexpr int k64x8r2 = 0, k32x8r1 = 1, k64x16r2 = 3, k128x16r2 = 4;                             // one step
     constexpr int t32x8 = 6, t64x8 = 7, t64x16t1024 = 8, t64x8t1024 = 10, t64x12t768 = 11;           // two steps
     const int E = p.order;
-    const bool cached = n < 1500000;   // from 2^19 nodes
+    const int64_t t8 = tiles_of(p, 64, 8), t16 = tiles_of(p, 64, 16), rounds16 = (t16 + 255) / 256;
+    const int64_t t128 = tiles_of(p, 128, 16);
+    // 64-wide columns that hang over, or a last round of blocks mostly empty
+    const bool poor64 = overhang(p, 64) > 1.2 || t16 * 5 < rounds16 * 256 * 4;
     if (p.precision != SC_FP64) {
-        if (n < (int64_t)1 << 17) return t64x8t1024;
+        if (n < (int64_t)1 << 19) {
+            if (p.lattice == SC_D2Q25 && E == 10 && t8 > 256)   // 64 x 16 does not fit
+                return tiles_of(p, 64, 12) <= 256 ? t64x12t768 : k64x16r2;
+            if (p.lattice == SC_D2Q25 && E == 4 && t8 > 512) return t64x8;
+            if (E == 10 && overhang(p, 64) > 1.2 && t8 > 256) return t8 <= 768 ? t32x8 : k32x8r1;
+            const int ty = two_step_height(p, p.lattice == SC_D2Q9 ? 1 : 2);
+            return ty == 8 ? t64x8t1024 : (ty == 12 ? t64x12t768 : t64x16t1024);
+        }
         if (p.lattice == SC_D2Q25) {
-            if (n < (int64_t)1 << 19) return E == 10 ? t64x8t1024 : t64x16t1024;
             if (E == 4) return t64x8;
-            if (cached) return k128x16r2;
+            if (n < 1500000) {
+                if (overhang(p, 128) > 1.15) return k64x16r2;
+                return t128 * 5 < (t128 + 255) / 256 * 256 * 4 && n < (int64_t)1 << 20 ? k32x8r1 : k128x16r2;
+            }
             return E == 10 ? t64x12t768 : t64x16t1024;
         }
-        if (n < (int64_t)1 << 19) return t64x16t1024;
         if (p.lattice == SC_D2Q9) return E == 10 ? t64x12t768 : t64x16t1024;
-        if (E == 10) return cached ? k128x16r2 : t64x8;
+        if (E == 10) return n < 3000000 ? k128x16r2 : t64x8;
         return E == 4 ? t64x16t1024 : t64x12t768;
     }
     if (p.lattice == SC_D2Q25) {
         if (E == 4) return t32x8;
         if (n < (int64_t)1 << 17) return k32x8r1;
-        return n < (int64_t)1 << 19 ? k64x16r2 : k64x8r2;
+        return n < (int64_t)1 << 20 ? (poor64 && n < (int64_t)1 << 19 ? k32x8r1 : k64x16r2) : k64x8r2;
     }
-    if (n < (int64_t)1 << 17) return t64x8t1024;
     if (p.lattice == SC_D2Q9) {
-        if (n < (int64_t)1 << 19) return t64x16t1024;
-        if (E == 4) return t32x8;
-        return E == 10 ? (cached ? k32x8r1 : t32x8) : t64x8;
+        if (n < (int64_t)1 << 17 && t8 <= 256) return t64x8t1024;
+        if (t16 <= 256) return t64x16t1024;
+        if (E == 10) return n < 1500000 ? k32x8r1 : t32x8;
+        return E == 4 || n < (int64_t)1 << 19 ? t32x8 : t64x8;
     }
-    if (n < (int64_t)1 << 19) return E == 4 ? t64x16t1024 : (E == 10 ? k64x16r2 : t64x8t1024);
-    if (E == 4) return t32x8;
-    return cached ? k128x16r2 : t64x12t768;
+    const int64_t t12 = tiles_of(p, 64, 12);
+    if (t8 <= 256) return t64x8t1024;
+    if (t12 <= (E == 10 ? 512 : 256)) return t64x12t768;
+    if (E < 10 && t8 <= 512) return t64x8t1024;
+    if (n < (int64_t)1 << 20) return k32x8r1;
+    if (E == 10 && n < 1500000) return k128x16r2;
+    return E == 4 ? t32x8 : t64x12t768;
 }
 
 // D3Q19: the persistent march with balanced segments, on 64 x 8 tiles in
