@@ -7,13 +7,13 @@
 // accumulates in FP32.  Padding is circular (the droplet domain is periodic).
 //
 // The 3 x 3 convolutions are dense contractions and run on the matrix cores:
-//   forward (32 output channels): per 16 x 16 pixel tile, out[p][co] =
-//     sum over 9 taps of x_t[p][ci] W_t[ci][co], one 16 x 16 x 32 bf16 MFMA
-//     per (16 pixels, 16 channels, tap).  The FP32 activations enter as the
-//     exact sum of three bf16 parts (hi + mid + lo, 8 significant bits each),
-//     so each product is the FP32 activation times the bf16 weight, exact,
-//     accumulated in FP32 -- three MFMAs per product, the price of keeping the
-//     activations in full FP32.
+//   forward (32 output channels): out[co][p] = sum over 9 taps of
+//     W_t[co][ci] x_t[ci][p], one 16 x 16 x 32 bf16 MFMA per (16 channels, 16
+//     pixels, tap).  The FP32 activations enter as the exact sum of three bf16
+//     parts (hi + mid + lo, 8 significant bits each), so each product is the
+//     FP32 activation times the bf16 weight, exact, accumulated in FP32 --
+//     three MFMAs per product, the price of keeping the activations in full
+//     FP32.
 //   backward-data: the forward kernel on the channel-transposed, spatially
 //     flipped weights.
 //   backward-weight: gW_t[co][ci] = sum_p g[co][p] x[ci][p + d_t], a
@@ -25,6 +25,8 @@
 // ALU: a 288-term dot product per pixel.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <algorithm>
 
 #include "../../include/sc_lbm.h"
 #include "kernels.h"   // xcd_swizzle
@@ -119,172 +121,237 @@ k_conv_fwd(const float* __restrict__ in, const uint16_t* __restrict__ w, const f
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// exact split of an FP32 value into three bf16 parts, v = hi + mid + lo:
-// each part truncates the remainder to its top 8 significant bits, and the
-// remainders are exact differences, so 24 bits are carried in all
-__device__ __forceinline__ void split3(float v, uint32_t& hi, uint32_t& mid, uint32_t& lo)
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// packed bf16 pairs (high halves) of two FP32 bit patterns: a in the low half
+__device__ __forceinline__ uint32_t pack_hi(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
+
+// Exact split of an FP32 value into three bf16 parts, v = hi + mid + lo: each
+// part truncates the remainder to its top 8 significant bits and the
+// remainders are exact differences, so 24 bits are carried in all.  The parts
+// are the top halves of u0, u1, u2.
+__device__ __forceinline__ void split3_bits(float v, uint32_t& u0, uint32_t& u1, uint32_t& u2)
 {
-    const uint32_t u = __float_as_uint(v);
-    const float r1 = v - __uint_as_float(u & 0xffff0000u);
-    const uint32_t u1 = __float_as_uint(r1);
-    const float r2 = r1 - __uint_as_float(u1 & 0xffff0000u);
-    hi = u >> 16;
-    mid = u1 >> 16;
-    lo = __float_as_uint(r2) >> 16;
+    u0 = __float_as_uint(v);
+    const float r1 = v - __uint_as_float(u0 & 0xffff0000u);
+    u1 = __float_as_uint(r1);
+    u2 = __float_as_uint(r1 - __uint_as_float(u1 & 0xffff0000u));
 }
 
 constexpr int kHaloPx = (TS + 2) * (TS + 2);   // pixels of a tile with its halo
-constexpr int kPxSlot = 32;                     // bf16 per pixel (or weight row) in LDS: 64 B
-constexpr int kPartBf = kHaloPx * kPxSlot;      // one bf16 part of the input tile
+constexpr int kPxSlot = 32;                     // bf16 per weight row in LDS: 64 B
 
 // LDS slot s holds 32 bf16 channels as four 16-byte chunks; chunk k is
 // stored at position k ^ ((s >> 2) & 3).  A quarter-wave reads one chunk of
 // 16 consecutive slots, which then fall on 16 distinct bank quads.
 __device__ __forceinline__ int slot_chunk(int s, int k) { return (k ^ (s >> 2)) & 3; }
 
-// Forward 3 x 3 convolution to 32 output channels on bf16 MFMAs.  A block
-// (4 waves) takes (image, 16 x 16 tile) work items in turn; wave v computes
-// tile rows 4v .. 4v+3.  LDS holds the input tile (halo 1, channels padded
-// to 32 with zeros) as three bf16 parts, pixel-major with the channels
-// contiguous, and the weights as [tap][co][ci] bf16, staged once per block
-// (80,640 B in all: two blocks share a CU, so one stages while the other
-// multiplies).  The tile's global loads are all issued before any is used:
-// one round trip per tile.  MFMA operands (16 x 16 x 32):
-// lane l supplies row or column l % 16 and the 8 consecutive k = 8 (l / 16)
-// ...; its accumulator holds rows 4 (l / 16) + i, column l % 16.  Here rows
-// are the pixels of a 16-pixel row segment, columns output channels and k
-// input channels.
-constexpr int kFwdStage = ((MAXC / 2) * kHaloPx + TS * TS - 1) / (TS * TS);   // staging loads per thread
-
 // Epilogue applied to each output before it is stored (fusing the
 // elementwise pass that would otherwise re-read the whole activation)
 enum ConvEpi { kEpiNone = 0, kEpiTanh = 1, kEpiTanhGrad = 2 };
 
 template <int EPI>
-__device__ __forceinline__ float conv_epi(float v, const float* __restrict__ y, int64_t i)
+__device__ __forceinline__ float conv_epi(float v, float yv)
 {
     if (EPI == kEpiTanh) return tanhf(v);
-    if (EPI == kEpiTanhGrad) {
-        const float yv = y[i];
-        return v * (1.f - yv * yv);
-    }
+    if (EPI == kEpiTanhGrad) return v * (1.f - yv * yv);
     return v;
 }
 
-template <int EPI>
-__global__ void __launch_bounds__(TS* TS, 2)
-k_conv_fwd_mfma(const float* __restrict__ in, const uint16_t* __restrict__ w, const float* __restrict__ bias,
-                float* __restrict__ out, const float* __restrict__ y, int batch, int cin, int h, int wd)
+typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
+
+// lane i of each 16 lanes takes src of lane i - 1 (lane 0: its own edge) or of
+// lane i + 1 (lane 15: its own edge)
+__device__ __forceinline__ u32x4 from_left(u32x4 edge, u32x4 src)
 {
-    __shared__ __align__(16) uint16_t xs[3 * kPartBf];
-    __shared__ __align__(16) uint16_t wsl[9 * MAXC * kPxSlot];
-    const int tid = threadIdx.y * TS + threadIdx.x;
-    const int lane = tid & 63, wv = tid >> 6;
-    const int r16 = lane & 15, kq = lane >> 4;
-    const int tiles_x = (wd + TS - 1) / TS, tiles = tiles_x * ((h + TS - 1) / TS);
-    const int nwork = tiles * batch;
-    const int64_t plane = (int64_t)h * wd;
-
-    for (int j = tid; j < 9 * MAXC * MAXC; j += TS * TS) {
-        const int t = j >> 10, co = (j >> 5) & 31, ci = j & 31;
-        const int sl = t * MAXC + co;
-        wsl[sl * kPxSlot + slot_chunk(sl, ci >> 3) * 8 + (ci & 7)] =
-            ci < cin ? w[((int64_t)co * cin + ci) * 9 + t] : (uint16_t)0;
-    }
-    float bv[2];
+    u32x4 d;
 #pragma unroll
-    for (int n = 0; n < 2; ++n) bv[n] = bias ? bias[n * 16 + r16] : 0.f;
-
-    // XCD-aware order: at any time the blocks of one XCD hold neighbouring
-    // tiles, so the cache lines two tiles share are fetched into one L2
-    for (int wi = xcd_swizzle(blockIdx.x, gridDim.x); wi < nwork; wi += gridDim.x) {
-        const int b = wi / tiles, tt = wi - b * tiles;
-        const int x0 = (tt % tiles_x) * TS, y0 = (tt / tiles_x) * TS;
-        const float* inb = in + (int64_t)b * cin * plane;
-        float v0[kFwdStage], v1[kFwdStage];
+    for (int i = 0; i < 4; ++i) d[i] = __builtin_amdgcn_update_dpp(edge[i], src[i], 0x111, 0xf, 0xf, false);
+    return d;
+}
+__device__ __forceinline__ u32x4 from_right(u32x4 edge, u32x4 src)
+{
+    u32x4 d;
 #pragma unroll
-        for (int q = 0; q < kFwdStage; ++q) {
-            const int j = tid + q * TS * TS;
-            v0[q] = v1[q] = 0.f;
-            if (j < (MAXC / 2) * kHaloPx) {
-                const int pr = j / kHaloPx, px = j - pr * kHaloPx;
-                const int ly = px / (TS + 2), lx = px - ly * (TS + 2);
-                // 32-bit element offsets within the image (checked on the host)
-                const uint32_t g = (uint32_t)(wrapc(y0 + ly - 1, h) * wd + wrapc(x0 + lx - 1, wd));
-                const uint32_t c = 2 * pr;
-                if ((int)c < cin) v0[q] = inb[c * (uint32_t)plane + g];
-                if ((int)c + 1 < cin) v1[q] = inb[(c + 1) * (uint32_t)plane + g];
-            }
-        }
-        __syncthreads();   // the previous item's reads of xs are done
-#pragma unroll
-        for (int q = 0; q < kFwdStage; ++q) {
-            const int j = tid + q * TS * TS;
-            if (j < (MAXC / 2) * kHaloPx) {
-                const int pr = j / kHaloPx, px = j - pr * kHaloPx;
-                uint32_t h0, m0, l0, h1, m1, l1;
-                split3(v0[q], h0, m0, l0);
-                split3(v1[q], h1, m1, l1);
-                uint32_t* d = (uint32_t*)(xs + px * kPxSlot + slot_chunk(px, pr >> 2) * 8 + 2 * (pr & 3));
-                d[0] = h0 | (h1 << 16);
-                d[kPartBf / 2] = m0 | (m1 << 16);
-                d[kPartBf] = l0 | (l1 << 16);
-            }
-        }
-        __syncthreads();
-
-        f32x4 acc[4][2];
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int n = 0; n < 2; ++n) acc[r][n] = f32x4{bv[n], bv[n], bv[n], bv[n]};
-#pragma unroll 1
-        for (int t = 0; t < 9; ++t) {   // rolled: unrolled, the scheduler hoists too many LDS reads
-            const int dy = t / 3, dx = t % 3;
-            const int s0 = t * MAXC + r16, s1 = s0 + 16;
-            const bf16x8 b0 = *(const bf16x8*)(wsl + s0 * kPxSlot + slot_chunk(s0, kq) * 8);
-            const bf16x8 b1 = *(const bf16x8*)(wsl + s1 * kPxSlot + slot_chunk(s1, kq) * 8);
-#pragma unroll
-            for (int part = 0; part < 3; ++part)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int px = (4 * wv + r + dy) * (TS + 2) + r16 + dx;
-                    const bf16x8 a = *(const bf16x8*)(xs + part * kPartBf + px * kPxSlot + slot_chunk(px, kq) * 8);
-                    acc[r][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b0, acc[r][0], 0, 0, 0);
-                    acc[r][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b1, acc[r][1], 0, 0, 0);
-                }
-        }
-        const int xq = x0 + 4 * kq;
-        const bool vec = (wd & 3) == 0 && xq + 3 < wd;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int yy = y0 + 4 * wv + r;
-            if (yy >= h) continue;
-#pragma unroll
-            for (int n = 0; n < 2; ++n) {
-                const int64_t o0 = ((int64_t)b * MAXC + n * 16 + r16) * plane + (int64_t)yy * wd + xq;
-                float* o = out + o0;
-                if (vec) {
-                    *(float4*)o = make_float4(conv_epi<EPI>(acc[r][n][0], y, o0), conv_epi<EPI>(acc[r][n][1], y, o0 + 1),
-                                              conv_epi<EPI>(acc[r][n][2], y, o0 + 2),
-                                              conv_epi<EPI>(acc[r][n][3], y, o0 + 3));
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (xq + i < wd) o[i] = conv_epi<EPI>(acc[r][n][i], y, o0 + i);
-                }
-            }
-        }
-    }
+    for (int i = 0; i < 4; ++i) d[i] = __builtin_amdgcn_update_dpp(edge[i], src[i], 0x101, 0xf, 0xf, false);
+    return d;
 }
 
-// wt[ci][co][8 - k] = w[co][ci][k]
-__global__ void k_transpose_flip(const uint16_t* __restrict__ w, uint16_t* __restrict__ wt, int cin, int cout)
+// 3 x 3 convolution to 32 channels (forward, and backward-data on the flipped,
+// transposed weights) on bf16 MFMAs, the activations going from global memory
+// to MFMA operands without LDS or barriers.
+//
+// A wave walks the rows of a 32-pixel strip.  The pixel operand's lane l holds
+// 8 channels (8 (l / 16) ...) of one pixel: per channel one 8-byte load of the
+// lane's two pixels x0 + 2 (l % 16) + {0, 1}, 128 contiguous bytes per channel.
+// The two pixels are two operands ("phases"), each value split exactly into
+// three bf16 parts; the three rows under the window stay in registers as
+// parts, so a row is loaded and split once per segment.  For the taps one column
+// to the left, phase 1's operand is phase 0 and phase 0's is phase 1 of the lane
+// before (DPP within 16 lanes); to the right likewise.  The strip's two outer
+// columns are a third operand (lane 0 of each 16 the left, the others the
+// right), only there to feed lanes 0 and 15 of those moves.
+//
+// MFMA rows are output channels (two tiles of 16), so a lane ends with its two
+// pixels of a channel: 8-byte stores, 128 bytes per channel.  The weights sit in
+// LDS as [tap][co][ci], read as 16-byte operands.
+//
+// Work units are (image, strip, row segment), the segment height balanced over
+// the resident waves (two per SIMD, so one's splits and epilogue run beside
+// the other's products).  The last strip of a row is moved left to end at the
+// image's edge and stores only its own pixels; NARROW: images narrower than a
+// strip, whose columns are loaded one by one, wrapped.
+//
+// What bounds it: memory and vector issue.  32 -> 32 at batch 16, 256 x 256 reads
+// and writes 268 MB (403 with the tanh derivative): 76 us plain (3.6 TB/s), 100
+// with the tanh, 110 with its derivative, where 16 x 16 tiles staged through
+// LDS took 110, 127 and 180; image sides that are no power of two run 10%
+// faster still.  Every accumulator sums the same products in the same order
+// as that kernel did: the outputs are the same to the bit.
+constexpr int kCPx = 32;        // pixels of a strip
+constexpr int kCWaves = 4;      // waves of a block, each with its own unit
+constexpr int kCBlocks = 2;     // blocks per CU
+
+template <bool ALL, int EPI, bool BWD, bool NARROW>
+__global__ void __launch_bounds__(64 * kCWaves, kCBlocks)
+k_conv_rows(const float* __restrict__ in, const uint16_t* __restrict__ w, const float* __restrict__ bias,
+            float* __restrict__ out, const float* __restrict__ y, int batch, int cin, int h, int wd, int seg_h,
+            int nseg)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= cin * cout * 9) return;
-    const int co = i / (cin * 9), r = i % (cin * 9), ci = r / 9, k = r % 9;
-    wt[((int64_t)ci * cout + co) * 9 + (8 - k)] = w[i];
+    __shared__ __align__(16) uint16_t wsl[9 * MAXC * kPxSlot];
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r16 = lane & 15, kq = lane >> 4;
+    const int64_t plane = (int64_t)h * wd;
+
+    // weights: operand row co, k = ci; the backward pass reads w[ci][co] with
+    // the taps reversed
+    for (int j = threadIdx.x; j < 9 * MAXC * MAXC; j += 64 * kCWaves) {
+        const int t = j >> 10, co = (j >> 5) & 31, ci = j & 31;
+        const int sl = t * MAXC + co;
+        const int64_t i = BWD ? ((int64_t)ci * MAXC + co) * 9 + 8 - t : ((int64_t)co * cin + ci) * 9 + t;
+        wsl[sl * kPxSlot + slot_chunk(sl, ci >> 3) * 8 + (ci & 7)] = ci < cin ? w[i] : (uint16_t)0;
+    }
+    __syncthreads();
+    f32x4 bv[2];
+#pragma unroll
+    for (int n = 0; n < 2; ++n)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) bv[n][i] = bias ? bias[n * 16 + 4 * kq + i] : 0.f;
+
+    const int strips = (wd + kCPx - 1) / kCPx;
+    const int nunits = strips * nseg * batch;
+    for (int u = xcd_swizzle(blockIdx.x, gridDim.x) * kCWaves + wv; u < nunits; u += gridDim.x * kCWaves) {
+        const int b = u / (strips * nseg), q = u - b * (strips * nseg);
+        const int sx = q / nseg, sy = q - sx * nseg;
+        const int y0 = sy * seg_h, y1 = y0 + seg_h < h ? y0 + seg_h : h;
+        const int xs = sx * kCPx;   // first pixel of the strip's own
+        const int x0 = NARROW || xs + kCPx <= wd ? xs : wd - kCPx;
+        const int p0 = x0 + 2 * r16;
+        const int c0 = ALL ? 8 * kq : 0;
+        const float* chan = in + ((int64_t)b * cin + c0) * plane;
+        const int xh = wrapc(r16 ? x0 + kCPx : x0 - 1, wd);
+        const int xa = NARROW ? wrapc(p0, wd) : p0, xb = NARROW ? wrapc(p0 + 1, wd) : p0 + 1;
+
+        struct Raw {
+            f32x2u v[8];
+            float e[8];
+        };
+        // a row in [-1, h + 1]; rows past a segment are loaded ahead and dropped
+        auto load = [&](int row, Raw& d) {
+            const int wr = row < 0 ? row + h : (row >= h ? row - h : row);
+            const float* pr = chan + (int64_t)(wr < h ? wr : h - 1) * wd;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const float* p = pr + (ALL ? c : (8 * kq + c < cin ? 8 * kq + c : 0)) * plane;
+                if (NARROW) d.v[c] = f32x2u{p[xa], p[xb]};
+                else d.v[c] = *(const f32x2u*)(p + p0);
+                d.e[c] = p[xh];
+            }
+        };
+        u32x4 pt[3][3][3];   // [row slot][phase, 2 = outer columns][part]
+        auto split = [&](const Raw& d, u32x4 (&o)[3][3]) {
+#pragma unroll
+            for (int f = 0; f < 3; ++f) {
+                uint32_t t[3][8];
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    float v = f < 2 ? d.v[c][f & 1] : d.e[c];
+                    if (!ALL) v = 8 * kq + c < cin ? v : 0.f;
+                    split3_bits(v, t[0][c], t[1][c], t[2][c]);
+                }
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    o[f][k] = u32x4{pack_hi(t[k][0], t[k][1]), pack_hi(t[k][2], t[k][3]), pack_hi(t[k][4], t[k][5]),
+                                    pack_hi(t[k][6], t[k][7])};
+            }
+        };
+
+        Raw raw;
+        load(y0 - 1, raw);
+        split(raw, pt[0]);
+        load(y0, raw);
+        split(raw, pt[1]);
+        load(y0 + 1, raw);
+        for (int r0 = y0; r0 < y1; r0 += 3) {
+#pragma unroll
+            for (int s = 0; s < 3; ++s) {
+                const int r = r0 + s;
+                if (r >= y1) continue;   // uniform
+                // rows r - 1, r, r + 1 are in slots s, s + 1, s + 2 (mod 3)
+                split(raw, pt[(s + 2) % 3]);
+                load(r + 2, raw);
+                const int64_t o0 = ((int64_t)b * MAXC + 4 * kq) * plane + (int64_t)r * wd + p0;
+                f32x2u yv[2][4];
+                if (EPI == kEpiTanhGrad)
+#pragma unroll
+                    for (int n = 0; n < 2; ++n)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const float* yp = y + o0 + (n * 16 + i) * plane;
+                            if (NARROW) yv[n][i] = f32x2u{p0 < wd ? yp[0] : 0.f, p0 + 1 < wd ? yp[1] : 0.f};
+                            else yv[n][i] = *(const f32x2u*)yp;
+                        }
+                __builtin_amdgcn_sched_barrier(0);   // the loads are issued before the products
+
+                f32x4 acc[2][2];   // [channel tile][phase]
+#pragma unroll
+                for (int n = 0; n < 2; ++n) acc[n][0] = acc[n][1] = bv[n];
+#pragma unroll
+                for (int t = 0; t < 9; ++t) {
+                    const int dx = t % 3, sr = (s + t / 3) % 3;
+                    const int s0 = t * MAXC + r16, s1 = s0 + 16;
+                    const bf16x8 w0 = *(const bf16x8*)(wsl + s0 * kPxSlot + slot_chunk(s0, kq) * 8);
+                    const bf16x8 w1 = *(const bf16x8*)(wsl + s1 * kPxSlot + slot_chunk(s1, kq) * 8);
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) {
+                        const u32x4 a0 = pt[sr][0][k], a1 = pt[sr][1][k], ah = pt[sr][2][k];
+                        const bf16x8 x0v = __builtin_bit_cast(bf16x8, dx == 0 ? from_left(ah, a1) : (dx == 1 ? a0 : a1));
+                        const bf16x8 x1v = __builtin_bit_cast(bf16x8, dx == 0 ? a0 : (dx == 1 ? a1 : from_right(ah, a0)));
+                        acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w0, x0v, acc[0][0], 0, 0, 0);
+                        acc[1][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1, x0v, acc[1][0], 0, 0, 0);
+                        acc[0][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w0, x1v, acc[0][1], 0, 0, 0);
+                        acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1, x1v, acc[1][1], 0, 0, 0);
+                    }
+                }
+#pragma unroll
+                for (int n = 0; n < 2; ++n)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        float* op = out + o0 + (n * 16 + i) * plane;
+                        const float e0 = conv_epi<EPI>(acc[n][0][i], yv[n][i][0]);
+                        const float e1 = conv_epi<EPI>(acc[n][1][i], yv[n][i][1]);
+                        if (!NARROW && x0 == xs) {   // uniform
+                            *(f32x2u*)op = f32x2u{e0, e1};
+                        } else {
+                            if (p0 >= xs && p0 < wd) op[0] = e0;
+                            if (p0 + 1 >= xs && p0 + 1 < wd) op[1] = e1;
+                        }
+                    }
+            }
+        }
+    }
 }
 
 // partial[blk][(ci*cout + co)*9 + k] and partial[blk][E + co] (bias): the
@@ -422,21 +489,6 @@ k_conv_bwd_w(const float* __restrict__ in, const float* __restrict__ gout, float
 // where staging the parts of a whole tile through block-wide LDS took 223 (16-bit
 // stores, one block per CU).  Every accumulator sums the same products in the
 // same order as that kernel did, so the gradients are the same to the bit.
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-
-// packed bf16 pairs (high halves) of two FP32 bit patterns: a in the low half
-__device__ __forceinline__ uint32_t pack_hi(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
-
-// the three bf16 parts of v as FP32 bit patterns whose top halves are the parts
-__device__ __forceinline__ void split3_bits(float v, uint32_t& u0, uint32_t& u1, uint32_t& u2)
-{
-    u0 = __float_as_uint(v);
-    const float r1 = v - __uint_as_float(u0 & 0xffff0000u);
-    u1 = __float_as_uint(r1);
-    u2 = __float_as_uint(r1 - __uint_as_float(u1 & 0xffff0000u));
-}
-
 // v with xcd_swizzle(v, nb) == L
 __device__ __forceinline__ int xcd_unswizzle(int L, int nb)
 {
@@ -451,9 +503,14 @@ constexpr int kWXRow = 24;                     // floats per input channel row: 
 constexpr int kWGRow = 20;                     // floats per gradient channel row
 constexpr int kWPatch = 4 * 16 * kWXRow + 2 * 16 * kWGRow;   // floats of a wave: two input pairs, one gradient pair
 
-// RAGGED: the image width is not a multiple of 16, columns are loaded one by
-// one, wrapped
-template <bool RAGGED>
+// EDGE: the image width is not a multiple of 16.  Lanes of the last tile whose
+// four pixels pass the image's edge load the row's last four and shift them;
+// the pixel beyond the edge, the wrapped first one, is the outer pixel of that
+// tile, and what lies past it meets a zero gradient.  kEdgeNarrow: fewer than
+// four columns, loaded one by one.
+enum WEdge { kEdgeNone = 0, kEdgeShift = 1, kEdgeNarrow = 2 };
+
+template <int EDGE>
 __global__ void __launch_bounds__(256 * kWGroups)
 k_conv_bwd_w_bf16(const float* __restrict__ in, const float* __restrict__ gout, float* __restrict__ partial,
                   int nblk, int batch, int h, int wd)
@@ -474,6 +531,9 @@ k_conv_bwd_w_bf16(const float* __restrict__ in, const float* __restrict__ gout, 
     const int64_t plane = (int64_t)h * wd;
     float* xpatch = lds + wv * kWPatch;
     float* gpatch = xpatch + 4 * 16 * kWXRow;
+    // positions that a narrow last tile leaves unwritten meet zero gradients
+    // and have to be numbers
+    for (int i = lane; i < kWPatch; i += 64) xpatch[i] = 0.f;
 
     f32x4 acc[9];
 #pragma unroll
@@ -485,6 +545,7 @@ k_conv_bwd_w_bf16(const float* __restrict__ in, const float* __restrict__ gout, 
     struct Raw {
         f32x4 x[2], g[2];
         float o;
+        int width, sh;   // columns of the tile inside the image (uniform); the lane's shift
     };
     struct Place {   // where a step's rows lie (uniform)
         int wi, s;
@@ -496,36 +557,39 @@ k_conv_bwd_w_bf16(const float* __restrict__ in, const float* __restrict__ gout, 
         const float* xb = in + ((int64_t)b * MAXC + nt * 16) * plane;
         const float* gb = gout + ((int64_t)b * MAXC + mt * 16) * plane;
         const int64_t cl = (int64_t)(lane >> 2) * plane;
-        int xc[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) xc[j] = RAGGED ? wrapc(x0 + 4 * (lane & 3) + j, wd) : x0 + 4 * (lane & 3) + j;
+        const int xw = x0 + 4 * (lane & 3);   // wanted and loaded column
+        const int xc = EDGE == kEdgeShift && xw > wd - 4 ? wd - 4 : xw;
+        auto four = [&](const float* row) {
+            if (EDGE == kEdgeNarrow)
+                return f32x4{row[wrapc(xw, wd)], row[wrapc(xw + 1, wd)], row[wrapc(xw + 2, wd)], row[wrapc(xw + 3, wd)]};
+            return (f32x4)*(const f32x4u*)(row + xc);
+        };
         int64_t xr[2];
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             xr[i] = (int64_t)wrapc(y0 - 1 + 2 * at.s + i, h) * wd;
             const int gy = y0 + 2 * at.s - 2 + i;   // s = 0 has no chunk: its gradient is dropped
             const int64_t gr = (int64_t)(gy < 0 ? 0 : (gy < h ? gy : h - 1)) * wd;
-            if (RAGGED) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    v.x[i][j] = xb[cl + xr[i] + xc[j]];
-                    v.g[i][j] = gb[cl + gr + xc[j]];
-                }
-            } else {
-                v.x[i] = *(const f32x4u*)(xb + cl + xr[i] + xc[0]);
-                v.g[i] = *(const f32x4u*)(gb + cl + gr + xc[0]);
-            }
+            v.x[i] = four(xb + cl + xr[i]);
+            v.g[i] = four(gb + cl + gr);
         }
-        v.o = xb[(int64_t)r16 * plane + (lane & 16 ? xr[1] : xr[0]) + wrapc(lane & 32 ? x0 + TS : x0 - 1, wd)];
+        v.width = EDGE != kEdgeNone && wd - x0 < TS ? wd - x0 : TS;
+        v.sh = EDGE == kEdgeShift ? xw - xc : 0;
+        v.o = xb[(int64_t)r16 * plane + (lane & 16 ? xr[1] : xr[0]) + wrapc(lane & 32 ? x0 + v.width : x0 - 1, wd)];
+    };
+    auto shifted = [](f32x4 v, int sh) {
+        if (EDGE != kEdgeShift) return v;
+        const f32x4 a = sh & 1 ? f32x4{v[1], v[2], v[3], v[3]} : v;
+        return sh & 2 ? f32x4{a[2], a[3], a[3], a[3]} : a;
     };
     // pair slot: 16 channels of two rows
     auto stage = [&](const Raw& v, int slot) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            *(f32x4*)(xpatch + ((2 * slot + i) * 16 + (lane >> 2)) * kWXRow + 4 + 4 * (lane & 3)) = v.x[i];
-            *(f32x4*)(gpatch + (i * 16 + (lane >> 2)) * kWGRow + 4 * (lane & 3)) = v.g[i];
+            *(f32x4*)(xpatch + ((2 * slot + i) * 16 + (lane >> 2)) * kWXRow + 4 + 4 * (lane & 3)) = shifted(v.x[i], v.sh);
+            *(f32x4*)(gpatch + (i * 16 + (lane >> 2)) * kWGRow + 4 * (lane & 3)) = shifted(v.g[i], v.sh);
         }
-        xpatch[((2 * slot + ((lane >> 4) & 1)) * 16 + r16) * kWXRow + (lane & 32 ? 20 : 3)] = v.o;
+        xpatch[((2 * slot + ((lane >> 4) & 1)) * 16 + r16) * kWXRow + (lane & 32 ? 4 + v.width : 3)] = v.o;
     };
     auto take_g = [&](float (&d)[8]) {
         const float* g = gpatch + (rs * 16 + r16) * kWGRow + c8;
@@ -570,13 +634,13 @@ k_conv_bwd_w_bf16(const float* __restrict__ in, const float* __restrict__ gout, 
     // gradient outside the image and of s = 0 enters as zero
     auto split_g = [&](const float (&v)[8], const Place& at, u32x4 (&d)[3]) {
         const int tt = at.wi % tiles;
-        const int left = RAGGED ? wd - (tt % tiles_x) * TS - c8 : 8;   // columns inside the image
+        const int left = EDGE != kEdgeNone ? wd - (tt % tiles_x) * TS - c8 : 8;   // columns inside the image
         const bool row = at.s > 0 && at.wi < nwork && active && (tt / tiles_x) * TS + 2 * at.s - 2 + rs < h;
         uint32_t t[3][8];
         float m[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            m[j] = row && (!RAGGED || j < left) ? v[j] : 0.f;
+            m[j] = row && (EDGE == kEdgeNone || j < left) ? v[j] : 0.f;
             split3_bits(m[j], t[0][j], t[1][j], t[2][j]);
         }
         bsum += ((m[0] + m[1]) + (m[2] + m[3])) + ((m[4] + m[5]) + (m[6] + m[7]));
@@ -884,21 +948,44 @@ static bool conv_shape_ok(int batch, int cin, int cout, int h, int w)
            batch <= 65535 && (int64_t)h * w * MAXC < ((int64_t)1 << 31);
 }
 
-// the 32-output-channel forward on the matrix cores, with its epilogue
-static hipError_t launch_fwd_mfma(int epi, const float* in, const uint16_t* w, const float* bias, float* out,
-                                  const float* y, int batch, int cin, int h, int wd, hipStream_t s)
+// Row-segment height of the row-walking convolution: `cols` strips of h rows
+// over `slots` resident waves.  A wave walks ceil(cols nseg / slots) segments of
+// H rows, each with about two rows' worth of start-up (the rows around it); the
+// height with the least total is taken.
+static int segment_height(int64_t cols, int h, int64_t slots)
 {
-    const int tiles = ((wd + TS - 1) / TS) * ((h + TS - 1) / TS);
-    const int64_t nwork = (int64_t)tiles * batch;
-    const int nb = (int)(nwork < 2 * cu_count() ? nwork : 2 * cu_count());
-    const dim3 block(TS, TS);
-    if (epi == kEpiTanh)
-        hipLaunchKernelGGL(k_conv_fwd_mfma<kEpiTanh>, dim3(nb), block, 0, s, in, w, bias, out, y, batch, cin, h, wd);
-    else if (epi == kEpiTanhGrad)
-        hipLaunchKernelGGL(k_conv_fwd_mfma<kEpiTanhGrad>, dim3(nb), block, 0, s, in, w, bias, out, y, batch, cin, h,
-                           wd);
-    else
-        hipLaunchKernelGGL(k_conv_fwd_mfma<kEpiNone>, dim3(nb), block, 0, s, in, w, bias, out, y, batch, cin, h, wd);
+    int best = h;
+    int64_t least = INT64_MAX;
+    const int64_t most = 4 * slots / cols + 4;   // beyond it every segment is start-up
+    for (int n = 1; n <= h && n <= most; ++n) {
+        const int H = (h + n - 1) / n;
+        const int64_t cost = (cols * ((h + H - 1) / H) + slots - 1) / slots * (H + 2);
+        if (cost < least) {
+            least = cost;
+            best = H;
+        }
+    }
+    return best;
+}
+
+// the convolution to 32 channels with its epilogue; BWD: w is the forward
+// weights of the layer whose input gradient this is
+template <int EPI, bool BWD>
+static hipError_t launch_rows(const float* in, const uint16_t* w, const float* bias, float* out, const float* y,
+                              int batch, int cin, int h, int wd, hipStream_t s)
+{
+    const int cols = (wd + kCPx - 1) / kCPx * batch;
+    const int64_t slots = (int64_t)cu_count() * kCBlocks * kCWaves;
+    const int seg_h = segment_height(cols, h, slots), nseg = (h + seg_h - 1) / seg_h;
+    const int64_t units = (int64_t)cols * nseg;
+    const int nb = (int)std::min<int64_t>((units + kCWaves - 1) / kCWaves, (int64_t)cu_count() * kCBlocks);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(nb), dim3(64 * kCWaves), 0, s, in, w, bias, out, y, batch, cin, h, wd, seg_h,
+                           nseg);
+    };
+    if (wd < kCPx) launch(k_conv_rows<false, EPI, BWD, true>);
+    else if (cin == MAXC) launch(k_conv_rows<true, EPI, BWD, false>);
+    else launch(k_conv_rows<false, EPI, BWD, false>);
     return hipGetLastError();
 }
 
@@ -907,7 +994,8 @@ extern "C" int sc_nn_conv3x3_fwd(const float* in, const uint16_t* w, const float
 {
     if (!in || !w || !out || !conv_shape_ok(batch, cin, cout, h, wd)) return SC_E_INVAL;
     if (cout == MAXC)
-        return nn_status(launch_fwd_mfma(kEpiNone, in, w, bias, out, nullptr, batch, cin, h, wd, (hipStream_t)stream));
+        return nn_status(
+            launch_rows<kEpiNone, false>(in, w, bias, out, nullptr, batch, cin, h, wd, (hipStream_t)stream));
     const int tiles = ((wd + TS - 1) / TS) * ((h + TS - 1) / TS);
     dim3 grid(tiles, batch), block(TS, TS);
     hipLaunchKernelGGL(k_conv_fwd<1>, grid, block, 0, (hipStream_t)stream, in, w, bias, out, cin, cout, h, wd);
@@ -918,21 +1006,19 @@ extern "C" int sc_nn_conv3x3_fwd_tanh(const float* in, const uint16_t* w, const 
                                       int32_t batch, int32_t cin, int32_t cout, int32_t h, int32_t wd, void* stream)
 {
     if (!in || !w || !out || !conv_shape_ok(batch, cin, cout, h, wd) || cout != MAXC) return SC_E_INVAL;
-    return nn_status(launch_fwd_mfma(kEpiTanh, in, w, bias, out, nullptr, batch, cin, h, wd, (hipStream_t)stream));
+    return nn_status(launch_rows<kEpiTanh, false>(in, w, bias, out, nullptr, batch, cin, h, wd, (hipStream_t)stream));
 }
 
+// gradient w.r.t. the input: convolution of gout (cout channels) with the
+// flipped, transposed weights (32 output channels), no bias; the kernel reads
+// the weights that way itself, and wt_scratch is not written
 extern "C" int sc_nn_conv3x3_bwd_data(const float* gout, const uint16_t* w, uint16_t* wt_scratch, float* gin,
                                       int32_t batch, int32_t cin, int32_t cout, int32_t h, int32_t wd, void* stream)
 {
     if (!gout || !w || !wt_scratch || !gin || !conv_shape_ok(batch, cin, cout, h, wd) || cin != MAXC)
         return SC_E_INVAL;
-    const int nw = cin * cout * 9;
-    hipLaunchKernelGGL(k_transpose_flip, (nw + 255) / 256, 256, 0, (hipStream_t)stream, w, wt_scratch, cin, cout);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return nn_status(e);
-    // gradient w.r.t. the input: convolution of gout (cout channels) with the
-    // flipped, transposed weights (cin output channels), no bias
-    return sc_nn_conv3x3_fwd(gout, wt_scratch, nullptr, gin, batch, cout, cin, h, wd, stream);
+    return nn_status(
+        launch_rows<kEpiNone, true>(gout, w, nullptr, gin, nullptr, batch, cout, h, wd, (hipStream_t)stream));
 }
 
 extern "C" int sc_nn_conv3x3_bwd_data_tanh(const float* gout, const uint16_t* w, uint16_t* wt_scratch, const float* y,
@@ -941,12 +1027,8 @@ extern "C" int sc_nn_conv3x3_bwd_data_tanh(const float* gout, const uint16_t* w,
 {
     if (!gout || !w || !wt_scratch || !y || !gin || !conv_shape_ok(batch, cin, cout, h, wd) || cin != MAXC)
         return SC_E_INVAL;
-    const int nw = cin * cout * 9;
-    hipLaunchKernelGGL(k_transpose_flip, (nw + 255) / 256, 256, 0, (hipStream_t)stream, w, wt_scratch, cin, cout);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return nn_status(e);
     return nn_status(
-        launch_fwd_mfma(kEpiTanhGrad, gout, wt_scratch, nullptr, gin, y, batch, cout, h, wd, (hipStream_t)stream));
+        launch_rows<kEpiTanhGrad, true>(gout, w, nullptr, gin, y, batch, cout, h, wd, (hipStream_t)stream));
 }
 
 extern "C" int32_t sc_nn_bwd_weight_scratch_floats(int32_t cin, int32_t cout, int32_t nblk)
@@ -962,13 +1044,15 @@ extern "C" int sc_nn_conv3x3_bwd_weight(const float* in, const float* gout, floa
         return SC_E_INVAL;
     const int E = cin * cout * 9;
     hipStream_t s = (hipStream_t)stream;
-    if (cin == MAXC && cout == MAXC)
-        if (wd % TS)
-            hipLaunchKernelGGL(k_conv_bwd_w_bf16<true>, (nblk + kWGroups - 1) / kWGroups, 256 * kWGroups, 0, s, in, gout,
-                               partial_scratch, nblk, batch, h, wd);
-        else
-            hipLaunchKernelGGL(k_conv_bwd_w_bf16<false>, (nblk + kWGroups - 1) / kWGroups, 256 * kWGroups, 0, s, in, gout,
-                               partial_scratch, nblk, batch, h, wd);
+    if (cin == MAXC && cout == MAXC) {
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, (nblk + kWGroups - 1) / kWGroups, 256 * kWGroups, 0, s, in, gout, partial_scratch,
+                               nblk, batch, h, wd);
+        };
+        if (wd % TS == 0) launch(k_conv_bwd_w_bf16<kEdgeNone>);
+        else if (wd >= 4) launch(k_conv_bwd_w_bf16<kEdgeShift>);
+        else launch(k_conv_bwd_w_bf16<kEdgeNarrow>);
+    }
     else
         hipLaunchKernelGGL(k_conv_bwd_w, nblk, dim3(TS, TS), 0, s, in, gout, partial_scratch, batch, cin, cout, h,
                            wd);
