@@ -17,10 +17,10 @@
 //   backward-data: the forward kernel on the channel-transposed, spatially
 //     flipped weights.
 //   backward-weight: gW_t[co][ci] = sum_p g[co][p] x[ci][p + d_t], a
-//     contraction over pixels, on FP32 16 x 16 x 4 MFMAs (both operands FP32:
-//     no splitting of the output gradient).  Per-block partial sums over a
-//     fixed share of (tile, image) pairs, then a column reduction in a fixed
-//     order (deterministic).
+//     contraction over pixels with both operands FP32: split into three bf16
+//     parts each (32 -> 32 channels) or on FP32 16 x 16 x 4 MFMAs (fewer).
+//     Partial sums over a fixed share of the (tile, image) pairs, then a
+//     column reduction in a fixed order (deterministic).
 // The one-output-channel forward (the net's last layer) stays on the vector
 // ALU: a 288-term dot product per pixel.
 #include <hip/hip_runtime.h>
@@ -139,7 +139,6 @@ __device__ __forceinline__ void split3_bits(float v, uint32_t& u0, uint32_t& u1,
     u2 = __float_as_uint(r1 - __uint_as_float(u1 & 0xffff0000u));
 }
 
-constexpr int kHaloPx = (TS + 2) * (TS + 2);   // pixels of a tile with its halo
 constexpr int kPxSlot = 32;                     // bf16 per weight row in LDS: 64 B
 
 // LDS slot s holds 32 bf16 channels as four 16-byte chunks; chunk k is
@@ -354,141 +353,6 @@ k_conv_rows(const float* __restrict__ in, const uint16_t* __restrict__ w, const 
     }
 }
 
-// partial[blk][(ci*cout + co)*9 + k] and partial[blk][E + co] (bias): the
-// block's share of (tile, image) pairs.  Per pair and tap t the gradient is a
-// contraction over the tile's 256 pixels, gW_t[co][ci] += g[co][p] x[ci][p +
-// d_t], on FP32 16 x 16 x 4 MFMAs: wave v owns the 16 x 16 block (co tile
-// v / 2, ci tile v % 2) of all nine taps (36 accumulator registers); k runs
-// over 4 consecutive pixels of a tile row.  LDS holds the output-gradient
-// tile [co][260] and the input tile with its halo [ci][18 x 18], both FP32;
-// the row strides (4 and 4 mod 64 banks) keep the 16 channel rows a
-// quarter-wave reads in distinct banks.
-constexpr int kGStride = TS * TS + 4;      // floats per output-gradient channel in LDS
-constexpr int kXStride = kHaloPx;          // floats per input channel in LDS (324 = 4 mod 64)
-
-__global__ void __launch_bounds__(TS* TS, 2)
-k_conv_bwd_w(const float* __restrict__ in, const float* __restrict__ gout, float* __restrict__ partial, int batch,
-             int cin, int cout, int h, int wd)
-{
-    __shared__ float gs[MAXC * kGStride];
-    __shared__ float xs[MAXC * kXStride];
-    const int tid = threadIdx.y * TS + threadIdx.x;
-    const int lane = tid & 63, wv = tid >> 6;
-    const int mt = wv >> 1, nt = wv & 1;   // co tile, ci tile of this wave
-    const int r16 = lane & 15, kq = lane >> 4;
-    const int tiles_x = (wd + TS - 1) / TS, tiles_y = (h + TS - 1) / TS;
-    const int nwork = tiles_x * tiles_y * batch;
-    const int64_t plane = (int64_t)h * wd;
-    const int E = cout * cin * 9;
-    const bool active = mt * 16 < cout && nt * 16 < cin;
-    f32x4 acc[9];
-#pragma unroll
-    for (int t = 0; t < 9; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float bacc = 0.f;
-    for (int wi = xcd_swizzle(blockIdx.x, gridDim.x); wi < nwork; wi += gridDim.x) {   // XCD-aware, as above
-        const int b = wi / (tiles_x * tiles_y), tt = wi % (tiles_x * tiles_y);
-        const int x0 = (tt % tiles_x) * TS, y0 = (tt / tiles_x) * TS;
-        // output-gradient tile, every channel (zero outside the image and
-        // for channels beyond cout), and the input tile with a wrapped halo
-        // of one (zero for channels beyond cin): every load issued first.
-        // Thread tid stages pixel tid of the tile and halo pixels tid and
-        // tid + 256 (the latter for tid < 68), all channels.
-        float gv[MAXC], xv[MAXC], xw[MAXC];
-        // 32-bit element offsets within the image (checked on the host)
-        const float* gb = gout + (int64_t)b * cout * plane;
-        const float* xb0 = in + (int64_t)b * cin * plane;
-        const bool two = tid + TS * TS < kHaloPx;
-        {
-            const int x = x0 + tid % TS, y = y0 + tid / TS;
-            const bool in_img = x < wd && y < h;
-            const uint32_t po = (uint32_t)(y * wd + x);
-            const int r1 = two ? tid + TS * TS : 0;
-            const uint32_t h0 = (uint32_t)(wrapc(y0 + tid / (TS + 2) - 1, h) * wd + wrapc(x0 + tid % (TS + 2) - 1, wd));
-            const uint32_t h1 = (uint32_t)(wrapc(y0 + r1 / (TS + 2) - 1, h) * wd + wrapc(x0 + r1 % (TS + 2) - 1, wd));
-#pragma unroll
-            for (int c = 0; c < MAXC; ++c) {
-                const uint32_t co = (uint32_t)c * (uint32_t)plane;
-                gv[c] = (c < cout && in_img) ? gb[co + po] : 0.f;
-                xv[c] = c < cin ? xb0[co + h0] : 0.f;
-                xw[c] = (two && c < cin) ? xb0[co + h1] : 0.f;
-            }
-        }
-        __syncthreads();   // the previous item's reads of gs and xs are done
-#pragma unroll
-        for (int c = 0; c < MAXC; ++c) {
-            gs[c * kGStride + tid] = gv[c];
-            xs[c * kXStride + tid] = xv[c];
-            if (two) xs[c * kXStride + tid + TS * TS] = xw[c];
-        }
-        __syncthreads();
-        {   // bias: thread (co = tid / 8, slice tid % 8) sums 32 pixels
-            const float* gr = gs + (tid >> 3) * kGStride + (tid & 7) * 32;
-            float sb = 0.f;
-#pragma unroll 8
-            for (int p = 0; p < 32; ++p) sb += gr[p];
-            bacc += sb;
-        }
-        if (!active) continue;   // this wave's co or ci tile lies wholly beyond cout or cin
-        const float* ga = gs + (mt * 16 + r16) * kGStride;
-        const float* xb = xs + (nt * 16 + r16) * kXStride;
-#pragma unroll 2
-        for (int ks = 0; ks < TS * TS / 4; ++ks) {
-            const int p = 4 * ks + kq;             // pixel of this lane's k
-            const int hp = (p / TS) * (TS + 2) + p % TS;   // its halo index at tap (0, 0)
-            const float av = ga[p];
-#pragma unroll
-            for (int t = 0; t < 9; ++t)
-                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, xb[hp + (t / 3) * (TS + 2) + t % 3], acc[t], 0, 0,
-                                                              0);
-        }
-    }
-    float* pb = partial + (int64_t)blockIdx.x * (E + cout);
-    const int ci = nt * 16 + r16;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int co = mt * 16 + 4 * kq + i;
-        if (ci < cin && co < cout)
-#pragma unroll
-            for (int t = 0; t < 9; ++t) pb[(ci * cout + co) * 9 + t] = acc[t][i];
-    }
-    // bias partial: the 8 slices of each channel, summed in a fixed order
-#pragma unroll
-    for (int off = 1; off < 8; off <<= 1) bacc += __shfl_xor(bacc, off, 64);
-    if ((tid & 7) == 0 && (tid >> 3) < cout) pb[E + (tid >> 3)] = bacc;
-}
-
-// The 32 -> 32 weight gradient on bf16 MFMAs.  The same contraction over
-// pixels, gW_t[co][ci] += g[co][p] x[ci][p + d_t], with both operands split
-// exactly into three bf16 parts and the six part products whose weights
-// reach 2^-24 summed (hi.hi, hi.mid, mid.hi, hi.lo, mid.mid, lo.hi): FP32
-// operands to within about 2^-24 of each product.
-//
-// Partial row v sums the 16 x 16 tiles xcd_swizzle(v) + k nblk, k = 0, 1, ...,
-// eight chunks of two tile rows (32 pixels, one MFMA's k) per tile.  A group
-// of four waves, one per 16 x 16 (co, ci) block of all nine taps, works on one
-// row; two groups share a block.  The waves run independently: each stages its
-// own 16 input and 16 gradient channels, two image rows at a time, through an
-// LDS patch of its own (FP32; 4 lanes load a channel row's 64 bytes, the patch
-// turns them into the operands' layout, 8 consecutive pixels of one channel
-// per lane) and splits them in registers.  No barrier in the loop.
-//
-// With pairs P_s = input rows (y0 - 1 + 2s, y0 + 2s), s = 0 .. 8, and M_s = the
-// second row of P_(s-1) with the first of P_s, chunk c multiplies its gradient
-// rows with P_c (dy = -1), M_(c+1) (dy = 0) and P_(c+1) (dy = +1).  The three
-// column shifts of an operand are the same ten split values packed in pairs
-// from three starts.  Software pipeline, per pair: pass the loaded rows through
-// the patch, issue the next loads, then the products of the chunk before run
-// beside the splits of this one.
-//
-// One barrier per tile keeps a block's waves on the same tiles: without it they
-// drift apart and fetch each line twice (553 against 276 MB at batch 16,
-// 256 x 256).
-//
-// What bounds it: vector issue and the matrix cores, 224 VALU instructions
-// beside 54 MFMAs per step and wave.  At batch 16, 256 x 256 it takes 147 us,
-// where staging the parts of a whole tile through block-wide LDS took 223 (16-bit
-// stores, one block per CU).  Every accumulator sums the same products in the
-// same order as that kernel did, so the gradients are the same to the bit.
 // v with xcd_swizzle(v, nb) == L
 __device__ __forceinline__ int xcd_unswizzle(int L, int nb)
 {
@@ -498,7 +362,16 @@ __device__ __forceinline__ int xcd_unswizzle(int L, int nb)
     return (m % q) * 8 + r + m / q;
 }
 
-constexpr int kWGroups = 2;                    // partial rows a block works on
+// ---- weight gradients --------------------------------------------------
+// gW_t[co][ci] = sum_p g[co][p] x[ci][p + d_t].  Partial row v sums the 16 x 16
+// tiles xcd_swizzle(v) + k nblk, k = 0, 1, ..., of all images; it is
+//   partial[v][(ci cout + co) 9 + t],  partial[v][cin cout 9 + co] (bias).
+// A wave owns a 16 x 16 (co, ci) block of all nine taps of one partial row and
+// takes its operands from an LDS patch of its own, so there is no barrier
+// between staging and products: two image rows ("a pair") of 16 input and 16
+// gradient channels at a time, FP32.  Input pair s of a tile holds rows
+// y0 - 1 + 2s and y0 + 2s, s = 0 .. 8; the gradient rows that come with it are
+// those of chunk s - 1, y0 + 2s - 2 and y0 + 2s - 1.
 constexpr int kWXRow = 24;                     // floats per input channel row: pixel p at 4 + p, outer pixels at 3 and 20
 constexpr int kWGRow = 20;                     // floats per gradient channel row
 constexpr int kWPatch = 4 * 16 * kWXRow + 2 * 16 * kWGRow;   // floats of a wave: two input pairs, one gradient pair
@@ -509,6 +382,251 @@ constexpr int kWPatch = 4 * 16 * kWXRow + 2 * 16 * kWGRow;   // floats of a wave
 // tile, and what lies past it meets a zero gradient.  kEdgeNarrow: fewer than
 // four columns, loaded one by one.
 enum WEdge { kEdgeNone = 0, kEdgeShift = 1, kEdgeNarrow = 2 };
+
+// Loads and stages pairs.  Lane l loads 4 pixels from 4 (l & 3) of channel l / 4
+// (four lanes a channel row's 64 bytes: with the operands' own layout, one
+// channel per lane, every lane would be a cache line of its own) and an outer
+// pixel of channel l & 15, row (l / 16) & 1, left or right by l / 32.
+template <int EDGE>
+struct PairStage {
+    const float *in, *gout;
+    int nwork, tiles, tiles_x, h, wd;
+    int cin, cout, c0, g0;   // channels of an image, and the wave's first
+    float* patch;
+
+    struct Raw {
+        f32x4 x[2], g[2];
+        float o;
+    };
+    // a tile: the lane's channel rows at its columns (narrow images: column 0),
+    // the first row, the columns inside the image and the lane's shift
+    struct Tile {
+        const float *x, *g, *o;
+        int y0, width, sh, col;
+        bool live;
+    };
+
+    // the patch starts as zeros: what a narrow last tile leaves unwritten has to
+    // be a number (it meets zero gradients)
+    __device__ __forceinline__ void clear(int lane) const
+    {
+        for (int i = lane; i < kWPatch; i += 64) patch[i] = 0.f;
+    }
+    // channels that do not exist are read as channel 0
+    __device__ __forceinline__ Tile tile(int at, int lane) const
+    {
+        Tile t;
+        const int64_t plane = (int64_t)h * wd;
+        const int wi = at < nwork ? at : nwork - 1;
+        const int b = wi / tiles, tt = wi - b * tiles;
+        const int x0 = (tt % tiles_x) * TS;
+        auto chan = [&](const float* base, int nc, int c) { return base + ((int64_t)b * nc + (c < nc ? c : 0)) * plane; };
+        const int xw = x0 + 4 * (lane & 3);   // wanted and loaded column
+        const int xc = EDGE == kEdgeNarrow ? 0 : (EDGE == kEdgeShift && xw > wd - 4 ? wd - 4 : xw);
+        t.y0 = (tt / tiles_x) * TS;
+        t.width = EDGE != kEdgeNone && wd - x0 < TS ? wd - x0 : TS;
+        t.sh = EDGE == kEdgeShift ? xw - xc : 0;
+        t.col = xw;
+        t.x = chan(in, cin, c0 + (lane >> 2)) + xc;
+        t.g = chan(gout, cout, g0 + (lane >> 2)) + xc;
+        t.o = chan(in, cin, c0 + (lane & 15)) + wrapc(lane & 32 ? x0 + t.width : x0 - 1, wd);
+        t.live = at < nwork;
+        return t;
+    }
+    // offset of input row r in [-1, TS h]: the wrapped row up to r = h; rows past
+    // it meet zero gradients and any will do
+    __device__ __forceinline__ int64_t row(int r) const
+    {
+        const int w = r < 0 ? h - 1 : (r == h ? 0 : (r < h ? r : h - 1));
+        return (int64_t)w * wd;
+    }
+    __device__ __forceinline__ f32x4 four(const float* p, const Tile& t) const
+    {
+        if (EDGE == kEdgeNarrow)
+            return f32x4{p[wrapc(t.col, wd)], p[wrapc(t.col + 1, wd)], p[wrapc(t.col + 2, wd)], p[wrapc(t.col + 3, wd)]};
+        return (f32x4)*(const f32x4u*)p;
+    }
+    __device__ __forceinline__ Raw load(const Tile& t, int s, int lane) const
+    {
+        Raw v;
+        int64_t xr[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            xr[i] = row(t.y0 - 1 + 2 * s + i);
+            const int gy = t.y0 + 2 * s - 2 + i;   // s = 0 has no chunk: its gradient is dropped
+            const int64_t gr = (int64_t)(gy < 0 ? 0 : (gy < h ? gy : h - 1)) * wd;
+            v.x[i] = four(t.x + xr[i], t);
+            v.g[i] = four(t.g + gr, t);
+        }
+        v.o = t.o[lane & 16 ? xr[1] : xr[0]];
+        return v;
+    }
+    static __device__ __forceinline__ f32x4 shifted(f32x4 v, int sh)
+    {
+        if (EDGE != kEdgeShift) return v;
+        const f32x4 a = sh & 1 ? f32x4{v[1], v[2], v[3], v[3]} : v;
+        return sh & 2 ? f32x4{a[2], a[3], a[3], a[3]} : a;
+    }
+    // row i of pair slot k (0 or 1) and of the gradient pair, channel c
+    __device__ __forceinline__ float* xrow(int k, int i, int c) const { return patch + ((2 * k + i) * 16 + c) * kWXRow + 4; }
+    __device__ __forceinline__ float* grow(int i, int c) const { return patch + 4 * 16 * kWXRow + (i * 16 + c) * kWGRow; }
+
+    __device__ __forceinline__ void stage(const Raw& v, const Tile& t, int slot, int lane) const
+    {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            *(f32x4*)(xrow(slot, i, lane >> 2) + 4 * (lane & 3)) = shifted(v.x[i], t.sh);
+            *(f32x4*)(grow(i, lane >> 2) + 4 * (lane & 3)) = shifted(v.g[i], t.sh);
+        }
+        xrow(slot, (lane >> 4) & 1, lane & 15)[lane & 32 ? t.width : -1] = v.o;
+    }
+    // whether gradient row i of pair s >= 1 counts
+    __device__ __forceinline__ bool counts(const Tile& t, int s, int i) const
+    {
+        return t.live && t.y0 + 2 * s - 2 + i < h;
+    }
+};
+
+// Layers with fewer than 32 channels on either side: FP32 16 x 16 x 4 MFMAs, k
+// running over 4 consecutive pixels of a tile row.  NB waves per partial row,
+// one per (co, ci) block, 4 / NB rows per block of four waves.
+// What bounds it: the FP32 matrix rate, 36 MFMAs of 32 cycles per tile row and
+// wave; 5 -> 32 channels at batch 16, 256 x 256 108 us (150 with tiles staged by
+// the whole block between two barriers), 32 -> 1 105 (197).  Each accumulator
+// adds its products in the same order as then.
+template <int NB, int EDGE>
+__global__ void __launch_bounds__(256)
+k_conv_bwd_w(const float* __restrict__ in, const float* __restrict__ gout, float* __restrict__ partial, int nblk,
+             int batch, int cin, int cout, int h, int wd)
+{
+    constexpr int GR = 4 / NB;   // partial rows a block works on
+    __shared__ __align__(16) float lds[4 * kWPatch];
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int grp = wv / NB, blk = wv % NB;
+    const int nci = cin > 16 ? 2 : 1;
+    const int mt = blk / nci, nt = blk % nci;
+    const int r16 = lane & 15, kq = lane >> 4;
+    const int L0 = xcd_swizzle(blockIdx.x, gridDim.x) * GR + grp;   // this row's first tile
+    const bool co_ok = mt * 16 + r16 < cout, ci_ok = nt * 16 + r16 < cin;
+    using PS = PairStage<EDGE>;
+    const int tiles_x = (wd + TS - 1) / TS, tiles = tiles_x * ((h + TS - 1) / TS);
+    const PS st{in, gout, tiles * batch, tiles, tiles_x, h, wd, cin, cout, nt * 16, mt * 16, lds + wv * kWPatch};
+    st.clear(lane);
+
+    f32x4 acc[9];
+#pragma unroll
+    for (int t = 0; t < 9; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float bsum = 0.f;
+    // every wave of the block takes the same number of tiles, so that all meet
+    // the barrier; without a tile of its own it adds zeros
+    // Pair s goes through raw[s mod 3], its loads two pairs ahead: one wave per
+    // SIMD has nothing else to cover them with.  Nor the LDS reads: row q of the
+    // tile's 18 input rows sits in xw[q mod 3], and the next input row and
+    // gradient row are read while this one's 36 products run.
+    typename PS::Tile t = st.tile(L0, lane), nxt;
+    typename PS::Raw raw[3] = {st.load(t, 0, lane), st.load(t, 1, lane), st.load(t, 2, lane)};
+    float g[2][4], xw[3][4][3];   // [4 px group][dx]
+    auto take_g = [&](int r, float (&d)[4]) {   // tile row r
+        const bool row = co_ok && t.live && t.y0 + r < h;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float v = st.grow(r & 1, r16)[4 * j + kq];
+            d[j] = row && (EDGE == kEdgeNone || 4 * j + kq < t.width) ? v : 0.f;
+        }
+    };
+    auto take_x = [&](int q, float (&d)[4][3]) {
+        const float* x = st.xrow((q >> 1) & 1, q & 1, r16) + kq - 1;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int dx = 0; dx < 3; ++dx) {
+                const float v = x[4 * j + dx];
+                d[j][dx] = ci_ok ? v : 0.f;
+            }
+    };
+    for (int wi = L0; wi < st.nwork + grp; wi += nblk) {
+        __builtin_amdgcn_s_barrier();
+        st.stage(raw[0], t, 0, lane);
+        raw[0] = st.load(t, 3, lane);
+        take_x(0, xw[0]);
+        take_x(1, xw[1]);
+        st.stage(raw[1], t, 1, lane);
+        raw[1] = st.load(t, 4, lane);
+        take_x(2, xw[2]);
+        take_g(0, g[0]);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            float xn[4][3];
+            if (r == 9) nxt = st.tile(wi + nblk, lane);
+            if (r < 15) {
+                if (r & 1) {   // input row r + 3 and gradient row r + 1 open pair s
+                    const int s = (r + 3) / 2;
+                    st.stage(raw[s % 3], t, s & 1, lane);
+                    raw[s % 3] = s < 6 ? st.load(t, s + 3, lane) : st.load(nxt, s - 6, lane);
+                }
+                take_x(r + 3, xn);
+                take_g(r + 1, g[(r + 1) & 1]);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+                    for (int dx = 0; dx < 3; ++dx)
+                        acc[3 * dy + dx] = __builtin_amdgcn_mfma_f32_16x16x4f32(g[r & 1][j], xw[(r + dy) % 3][j][dx],
+                                                                                acc[3 * dy + dx], 0, 0, 0);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                bsum += g[r & 1][j];
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx) xw[r % 3][j][dx] = r < 15 ? xn[j][dx] : 0.f;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        t = nxt;
+    }
+    if (L0 >= nblk) return;
+    const int E = cin * cout * 9;
+    float* pb = partial + (int64_t)xcd_unswizzle(L0, nblk) * (E + cout);
+    const int ci = nt * 16 + r16;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int co = mt * 16 + 4 * kq + i;
+        if (ci < cin && co < cout)
+#pragma unroll
+            for (int t = 0; t < 9; ++t) pb[(ci * cout + co) * 9 + t] = acc[t][i];
+    }
+    // bias: the four pixel classes of a channel
+    bsum += __shfl_xor(bsum, 16, 64);
+    bsum += __shfl_xor(bsum, 32, 64);
+    if (nt == 0 && kq == 0 && co_ok) pb[E + mt * 16 + r16] = bsum;
+}
+
+// The 32 -> 32 weight gradient on bf16 MFMAs: both operands split exactly into
+// three bf16 parts and the six part products whose weights reach 2^-24 summed
+// (hi.hi, hi.mid, mid.hi, hi.lo, mid.mid, lo.hi): FP32 operands to within about
+// 2^-24 of each product.  k runs over the 32 pixels of a chunk (two tile rows),
+// 8 consecutive pixels of one row per lane; the splits are made in registers.
+// Four waves per partial row, two rows per block.
+//
+// With input pairs P_s and M_s = the second row of P_(s-1) with the first of
+// P_s, chunk c multiplies its gradient rows with P_c (dy = -1), M_(c+1) (dy =
+// 0) and P_(c+1) (dy = +1).  The three column shifts of an operand are the same
+// ten split values packed in pairs from three starts.  Software pipeline, per
+// pair: pass the loaded rows through the patch, issue the next loads, then the
+// products of the chunk before run beside the splits of this one.
+//
+// One barrier per tile keeps a block's waves on the same tiles: without it they
+// drift apart and fetch each line twice (553 against 276 MB at batch 16,
+// 256 x 256).
+//
+// What bounds it: vector issue and the matrix cores, 224 VALU instructions
+// beside 54 MFMAs per step and wave.  At batch 16, 256 x 256 it takes 135 - 147
+// us, where staging the parts of a whole tile through block-wide LDS took 223
+// (16-bit stores, one block per CU).  Every accumulator sums the same products
+// in the same order as that kernel did, so the gradients are the same to the bit.
+constexpr int kWGroups = 2;                    // partial rows a block works on
 
 template <int EDGE>
 __global__ void __launch_bounds__(256 * kWGroups)
@@ -523,76 +641,19 @@ k_conv_bwd_w_bf16(const float* __restrict__ in, const float* __restrict__ gout, 
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int grp = wv >> 2, mt = (wv >> 1) & 1, nt = wv & 1;
     const int r16 = lane & 15, kq = lane >> 4, rs = kq >> 1, c8 = 8 * (kq & 1);
-    const int L0 = xcd_swizzle(blockIdx.x, gridDim.x) * kWGroups + grp;   // this group's first tile
-    const bool active = L0 < nblk;
+    const int L0 = xcd_swizzle(blockIdx.x, gridDim.x) * kWGroups + grp;   // this row's first tile
+    using PS = PairStage<EDGE>;
     const int tiles_x = (wd + TS - 1) / TS, tiles = tiles_x * ((h + TS - 1) / TS);
-    const int nwork = tiles * batch;
-    const int wend = nwork + grp;   // the block's groups take equally many tiles
-    const int64_t plane = (int64_t)h * wd;
-    float* xpatch = lds + wv * kWPatch;
-    float* gpatch = xpatch + 4 * 16 * kWXRow;
-    // positions that a narrow last tile leaves unwritten meet zero gradients
-    // and have to be numbers
-    for (int i = lane; i < kWPatch; i += 64) xpatch[i] = 0.f;
+    const PS st{in, gout, tiles * batch, tiles, tiles_x, h, wd, MAXC, MAXC, nt * 16, mt * 16, lds + wv * kWPatch};
+    st.clear(lane);
 
     f32x4 acc[9];
 #pragma unroll
     for (int t = 0; t < 9; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     float bsum = 0.f;
 
-    // loading lane: 4 pixels from 4 (lane & 3) of channel lane / 4; outer
-    // pixels: channel lane & 15 of row (lane / 16) & 1, left or right by lane / 32
-    struct Raw {
-        f32x4 x[2], g[2];
-        float o;
-        int width, sh;   // columns of the tile inside the image (uniform); the lane's shift
-    };
-    struct Place {   // where a step's rows lie (uniform)
-        int wi, s;
-    };
-    auto load = [&](const Place& at, Raw& v) {
-        const int wi = at.wi < nwork ? at.wi : nwork - 1;
-        const int b = wi / tiles, tt = wi - b * tiles;
-        const int x0 = (tt % tiles_x) * TS, y0 = (tt / tiles_x) * TS;
-        const float* xb = in + ((int64_t)b * MAXC + nt * 16) * plane;
-        const float* gb = gout + ((int64_t)b * MAXC + mt * 16) * plane;
-        const int64_t cl = (int64_t)(lane >> 2) * plane;
-        const int xw = x0 + 4 * (lane & 3);   // wanted and loaded column
-        const int xc = EDGE == kEdgeShift && xw > wd - 4 ? wd - 4 : xw;
-        auto four = [&](const float* row) {
-            if (EDGE == kEdgeNarrow)
-                return f32x4{row[wrapc(xw, wd)], row[wrapc(xw + 1, wd)], row[wrapc(xw + 2, wd)], row[wrapc(xw + 3, wd)]};
-            return (f32x4)*(const f32x4u*)(row + xc);
-        };
-        int64_t xr[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            xr[i] = (int64_t)wrapc(y0 - 1 + 2 * at.s + i, h) * wd;
-            const int gy = y0 + 2 * at.s - 2 + i;   // s = 0 has no chunk: its gradient is dropped
-            const int64_t gr = (int64_t)(gy < 0 ? 0 : (gy < h ? gy : h - 1)) * wd;
-            v.x[i] = four(xb + cl + xr[i]);
-            v.g[i] = four(gb + cl + gr);
-        }
-        v.width = EDGE != kEdgeNone && wd - x0 < TS ? wd - x0 : TS;
-        v.sh = EDGE == kEdgeShift ? xw - xc : 0;
-        v.o = xb[(int64_t)r16 * plane + (lane & 16 ? xr[1] : xr[0]) + wrapc(lane & 32 ? x0 + v.width : x0 - 1, wd)];
-    };
-    auto shifted = [](f32x4 v, int sh) {
-        if (EDGE != kEdgeShift) return v;
-        const f32x4 a = sh & 1 ? f32x4{v[1], v[2], v[3], v[3]} : v;
-        return sh & 2 ? f32x4{a[2], a[3], a[3], a[3]} : a;
-    };
-    // pair slot: 16 channels of two rows
-    auto stage = [&](const Raw& v, int slot) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            *(f32x4*)(xpatch + ((2 * slot + i) * 16 + (lane >> 2)) * kWXRow + 4 + 4 * (lane & 3)) = shifted(v.x[i], v.sh);
-            *(f32x4*)(gpatch + (i * 16 + (lane >> 2)) * kWGRow + 4 * (lane & 3)) = shifted(v.g[i], v.sh);
-        }
-        xpatch[((2 * slot + ((lane >> 4) & 1)) * 16 + r16) * kWXRow + (lane & 32 ? 4 + v.width : 3)] = v.o;
-    };
     auto take_g = [&](float (&d)[8]) {
-        const float* g = gpatch + (rs * 16 + r16) * kWGRow + c8;
+        const float* g = st.grow(rs, r16) + c8;
         const f32x4 g0 = *(const f32x4*)g, g1 = *(const f32x4*)(g + 4);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -600,10 +661,10 @@ k_conv_bwd_w_bf16(const float* __restrict__ in, const float* __restrict__ gout, 
             d[4 + j] = g1[j];
         }
     };
-    // rows (a, b) for the lanes of the first and the second row; row k of slot
-    // s is 2 s + k
+    // rows (a, b) for the lanes of the first and the second row; row i of slot
+    // k is 2 k + i
     auto take_x = [&](int a, int b, float (&d)[10]) {
-        const float* p = xpatch + ((rs ? b : a) * 16 + r16) * kWXRow + 4 + c8;
+        const float* p = st.xrow(0, rs ? b : a, r16) + c8;
         const f32x4 p0 = *(const f32x4*)p, p1 = *(const f32x4*)(p + 4);
         d[0] = p[-1];
         d[9] = p[8];
@@ -632,22 +693,20 @@ k_conv_bwd_w_bf16(const float* __restrict__ in, const float* __restrict__ gout, 
         }
     };
     // gradient outside the image and of s = 0 enters as zero
-    auto split_g = [&](const float (&v)[8], const Place& at, u32x4 (&d)[3]) {
-        const int tt = at.wi % tiles;
-        const int left = EDGE != kEdgeNone ? wd - (tt % tiles_x) * TS - c8 : 8;   // columns inside the image
-        const bool row = at.s > 0 && at.wi < nwork && active && (tt / tiles_x) * TS + 2 * at.s - 2 + rs < h;
-        uint32_t t[3][8];
+    auto split_g = [&](const float (&v)[8], const typename PS::Tile& t, int s, u32x4 (&d)[3]) {
+        const bool row = st.counts(t, s, rs);
+        uint32_t u[3][8];
         float m[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            m[j] = row && (EDGE == kEdgeNone || j < left) ? v[j] : 0.f;
-            split3_bits(m[j], t[0][j], t[1][j], t[2][j]);
+            m[j] = row && (EDGE == kEdgeNone || c8 + j < t.width) ? v[j] : 0.f;
+            split3_bits(m[j], u[0][j], u[1][j], u[2][j]);
         }
         bsum += ((m[0] + m[1]) + (m[2] + m[3])) + ((m[4] + m[5]) + (m[6] + m[7]));
 #pragma unroll
         for (int k = 0; k < 3; ++k)
-            d[k] = u32x4{pack_hi(t[k][0], t[k][1]), pack_hi(t[k][2], t[k][3]), pack_hi(t[k][4], t[k][5]),
-                         pack_hi(t[k][6], t[k][7])};
+            d[k] = u32x4{pack_hi(u[k][0], u[k][1]), pack_hi(u[k][2], u[k][3]), pack_hi(u[k][4], u[k][5]),
+                         pack_hi(u[k][6], u[k][7])};
     };
 
     Part P[2][3], M[3];
@@ -675,62 +734,61 @@ k_conv_bwd_w_bf16(const float* __restrict__ in, const float* __restrict__ gout, 
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    // every wave of the block takes the same number of tiles, so that the
-    // barrier below is met by all; a group without a tile works on the last
-    // one with zero gradients
-    if (nwork > 0) {
-        Raw raw;
-        float gv[8], xv[10], mv[10];
-        load(Place{L0, 0}, raw);
-        stage(raw, 0);
-        load(Place{L0, 1}, raw);
-        take_x(0, 1, xv);
-        split_x(xv, P[0]);
-        for (int wi = L0; wi < wend; wi += nblk) {
-            __builtin_amdgcn_s_barrier();
-            // P[0] = P_0 of this tile.  Step s = 1 has no chunk before it.
-            stage(raw, 1);
+    // every wave of the block takes the same number of tiles, so that all meet
+    // the barrier; without a tile of its own it adds zeros
+    typename PS::Tile t = st.tile(L0, lane);
+    typename PS::Raw raw = st.load(t, 0, lane);
+    float gv[8], xv[10], mv[10];
+    st.stage(raw, t, 0, lane);
+    raw = st.load(t, 1, lane);
+    take_x(0, 1, xv);
+    split_x(xv, P[0]);
+    for (int wi = L0; wi < st.nwork + grp; wi += nblk) {
+        __builtin_amdgcn_s_barrier();
+        // P[0] = P_0 of this tile.  Step s = 1 has no chunk before it.
+        st.stage(raw, t, 1, lane);
+        take_g(gv);
+        take_x(2, 3, xv);
+        take_x(1, 2, mv);
+        raw = st.load(t, 2, lane);
+        split_g(gv, t, 1, G[1]);
+        split_x(xv, P[1]);
+        split_x(mv, M);
+        const typename PS::Tile nxt = st.tile(wi + nblk, lane);
+        // step s, pair slot s & 1: the products of chunk s - 2 beside the splits of chunk s - 1
+        auto step = [&](int slot, int s, const typename PS::Tile& ahead, int as) {
+            st.stage(raw, t, slot, lane);
             take_g(gv);
-            take_x(2, 3, xv);
-            take_x(1, 2, mv);
-            load(Place{wi, 2}, raw);
-            split_g(gv, Place{wi, 1}, G[1]);
-            split_x(xv, P[1]);
-            split_x(mv, M);
-            // step s, pair slot s & 1: the products of chunk s - 2 beside the splits of chunk s - 1
-            auto step = [&](int slot, int s, const Place& ahead) {
-                stage(raw, slot);
-                take_g(gv);
-                load(ahead, raw);
-                __builtin_amdgcn_sched_barrier(0);
-                take_x(2 * slot, 2 * slot + 1, xv);
-                products(P[slot], G[slot ^ 1], 0);
-                split_g(gv, Place{wi, s}, G[slot]);
-                mix();
-                take_x(2 * (slot ^ 1) + 1, 2 * slot, mv);
-                products(M, G[slot ^ 1], 1);
-                split_x(xv, P[slot]);
-                mix();
-                products(P[slot ^ 1], G[slot ^ 1], 2);
-                split_x(mv, M);
-                mix();
-            };
-#pragma unroll 1
-            for (int s = 2; s < 8; s += 2) {
-                step(0, s, Place{wi, s + 1});
-                step(1, s + 1, Place{wi, s + 2});
-            }
-            step(0, 8, Place{wi + nblk, 0});
-            // the last chunk beside the next tile's first pair
-            stage(raw, 0);
-            load(Place{wi + nblk, 1}, raw);
+            raw = st.load(ahead, as, lane);
             __builtin_amdgcn_sched_barrier(0);
-            take_x(0, 1, xv);
-            products(P[1], G[0], 0);
-            products(M, G[0], 1);
-            products(P[0], G[0], 2);
-            split_x(xv, P[0]);
+            take_x(2 * slot, 2 * slot + 1, xv);
+            products(P[slot], G[slot ^ 1], 0);
+            split_g(gv, t, s, G[slot]);
+            mix();
+            take_x(2 * (slot ^ 1) + 1, 2 * slot, mv);
+            products(M, G[slot ^ 1], 1);
+            split_x(xv, P[slot]);
+            mix();
+            products(P[slot ^ 1], G[slot ^ 1], 2);
+            split_x(mv, M);
+            mix();
+        };
+#pragma unroll 1
+        for (int s = 2; s < 8; s += 2) {
+            step(0, s, t, s + 1);
+            step(1, s + 1, t, s + 2);
         }
+        step(0, 8, nxt, 0);
+        // the last chunk beside the next tile's first pair
+        st.stage(raw, nxt, 0, lane);
+        raw = st.load(nxt, 1, lane);
+        __builtin_amdgcn_sched_barrier(0);
+        take_x(0, 1, xv);
+        products(P[1], G[0], 0);
+        products(M, G[0], 1);
+        products(P[0], G[0], 2);
+        split_x(xv, P[0]);
+        t = nxt;
     }
     __syncthreads();   // every wave is done with its patch
 
@@ -744,7 +802,7 @@ k_conv_bwd_w_bf16(const float* __restrict__ in, const float* __restrict__ gout, 
     bsum += __shfl_xor(bsum, 32, 64);
     if (nt == 0 && kq == 0) redb[grp * MAXC + mt * 16 + r16] = bsum;
     __syncthreads();
-    if (!active) return;
+    if (L0 >= nblk) return;
     float* pb = partial + (int64_t)xcd_unswizzle(L0, nblk) * (E + MAXC);
     const int t4 = threadIdx.x & 255;
     for (int e = t4; e < E; e += 256) pb[e] = red[e];
@@ -1044,18 +1102,30 @@ extern "C" int sc_nn_conv3x3_bwd_weight(const float* in, const float* gout, floa
         return SC_E_INVAL;
     const int E = cin * cout * 9;
     hipStream_t s = (hipStream_t)stream;
+    const int edge = wd % TS == 0 ? kEdgeNone : (wd >= 4 ? kEdgeShift : kEdgeNarrow);
     if (cin == MAXC && cout == MAXC) {
         auto launch = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, (nblk + kWGroups - 1) / kWGroups, 256 * kWGroups, 0, s, in, gout, partial_scratch,
                                nblk, batch, h, wd);
         };
-        if (wd % TS == 0) launch(k_conv_bwd_w_bf16<kEdgeNone>);
-        else if (wd >= 4) launch(k_conv_bwd_w_bf16<kEdgeShift>);
+        if (edge == kEdgeNone) launch(k_conv_bwd_w_bf16<kEdgeNone>);
+        else if (edge == kEdgeShift) launch(k_conv_bwd_w_bf16<kEdgeShift>);
         else launch(k_conv_bwd_w_bf16<kEdgeNarrow>);
+    } else {
+        const int nb = (cout > 16 ? 2 : 1) * (cin > 16 ? 2 : 1);   // waves per partial row
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, (nblk + 4 / nb - 1) / (4 / nb), 256, 0, s, in, gout, partial_scratch, nblk, batch,
+                               cin, cout, h, wd);
+        };
+        auto pick = [&](auto none, auto shift, auto narrow) {
+            if (edge == kEdgeNone) launch(none);
+            else if (edge == kEdgeShift) launch(shift);
+            else launch(narrow);
+        };
+        if (nb == 4) pick(k_conv_bwd_w<4, kEdgeNone>, k_conv_bwd_w<4, kEdgeShift>, k_conv_bwd_w<4, kEdgeNarrow>);
+        else if (nb == 2) pick(k_conv_bwd_w<2, kEdgeNone>, k_conv_bwd_w<2, kEdgeShift>, k_conv_bwd_w<2, kEdgeNarrow>);
+        else pick(k_conv_bwd_w<1, kEdgeNone>, k_conv_bwd_w<1, kEdgeShift>, k_conv_bwd_w<1, kEdgeNarrow>);
     }
-    else
-        hipLaunchKernelGGL(k_conv_bwd_w, nblk, dim3(TS, TS), 0, s, in, gout, partial_scratch, batch, cin, cout, h,
-                           wd);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return nn_status(e);
     hipLaunchKernelGGL(k_sum_partials, (E + cout + kSumCols - 1) / kSumCols, kSumCols * kSumGroups, 0, s,
