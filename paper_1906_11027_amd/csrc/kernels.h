@@ -429,7 +429,7 @@ struct ObsBuffers {
     double* F;        // [D][N]
     double* u;        // [D][N]
     double* partials; // [nblk][kObsSlots]
-    double* result;   // [kObsSlots]
+    double* result;   // [kCheckSlots]
     int nblk;
 };
 hipError_t launch_macro(int lattice, int precision, const void* f, const void* args, ObsBuffers& ob,
@@ -437,7 +437,9 @@ hipError_t launch_macro(int lattice, int precision, const void* f, const void* a
 hipError_t launch_force(int dim, int precision, int order, const void* args, ObsBuffers& ob,
                         bool with_velocity, hipStream_t s);
 hipError_t launch_psi_from_host(int precision, const double* psi_dev_d, void* psi, int64_t n, hipStream_t s);
-hipError_t launch_reduce(int dim, ObsBuffers& ob, const uint8_t* solid, int64_t n, hipStream_t s);
+// slots of the whole grid, then rho and psi at nodes ic and 0
+hipError_t launch_reduce(int dim, int precision, ObsBuffers& ob, const uint8_t* solid, int64_t n, int64_t ic,
+                         hipStream_t s);
 // dst[i] = (double)src[i], i < n
 hipError_t launch_widen(const float* src, double* dst, int64_t n, hipStream_t s);
 

@@ -156,9 +156,18 @@ k_reduce_partials(const double* __restrict__ rho, const double* __restrict__ u, 
     block_reduce_store(acc, partials + (int64_t)blockIdx.x * kNR);
 }
 
+// rho != null: also rho and psi (FP64 where psi64) at nodes ic and 0, behind the
+// slots, so that one copy brings the observables to the host
 __global__ void __launch_bounds__(kRedThreads)
-k_reduce_final(const double* __restrict__ partials, int nblk, double* __restrict__ out)
+k_reduce_final(const double* __restrict__ partials, int nblk, double* __restrict__ out,
+               const double* __restrict__ rho = nullptr, const void* __restrict__ psi = nullptr, int psi64 = 0,
+               int64_t ic = 0)
 {
+    if (rho && threadIdx.x < 2) {
+        const int64_t i = threadIdx.x == 0 ? ic : 0;
+        out[kObsSlots + 2 * threadIdx.x] = rho[i];
+        out[kObsSlots + 2 * threadIdx.x + 1] = psi64 ? ((const double*)psi)[i] : (double)((const float*)psi)[i];
+    }
     double acc[kNR];
 #pragma unroll
     for (int k = 0; k < kNR; ++k) acc[k] = slot_start(k);
@@ -316,12 +325,14 @@ hipError_t launch_widen(const float* src, double* dst, int64_t n, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_reduce(int dim, ObsBuffers& ob, const uint8_t* solid, int64_t n, hipStream_t s)
+hipError_t launch_reduce(int dim, int precision, ObsBuffers& ob, const uint8_t* solid, int64_t n, int64_t ic,
+                         hipStream_t s)
 {
     hipLaunchKernelGGL(k_reduce_partials, ob.nblk, kRedThreads, 0, s, ob.rho, ob.u, solid, dim, n, ob.partials);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_reduce_final, 1, kRedThreads, 0, s, ob.partials, ob.nblk, ob.result);
+    hipLaunchKernelGGL(k_reduce_final, 1, kRedThreads, 0, s, ob.partials, ob.nblk, ob.result, ob.rho, ob.psi, precision,
+                       ic);
     return hipGetLastError();
 }
 
@@ -354,7 +365,8 @@ static hipError_t check_launch(const StepArgs<T>& a, double* partials, double* r
                        partials, result + kObsSlots);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_reduce_final, 1, kRedThreads, 0, s, partials, nb, result);
+    hipLaunchKernelGGL(k_reduce_final, 1, kRedThreads, 0, s, partials, nb, result, (const double*)nullptr,
+                       (const void*)nullptr, 0, (int64_t)0);
     return hipGetLastError();
 }
 

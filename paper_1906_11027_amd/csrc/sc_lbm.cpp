@@ -33,8 +33,11 @@ constexpr int kBatchShapeFP64 = 2;
 constexpr int kFloorWindow = 50;   // checks the FP32 resolution rule fits a line to
 constexpr int kFloorHorizon = 300; // checks ahead over which that line's drift must stay in the band
 
+// observation fields and partials, carved from one allocation: the handle's
+// own (base), or one that the items of a batch share (base null)
 struct ObsState {
     bool ready = false;
+    void* base = nullptr;
     ObsBuffers b{};
 };
 
@@ -549,29 +552,21 @@ static void release(sc_lbm* h)
 {
     if (!h) return;
     drop_graphs(h);
-    hipFree(h->chk_partials);
-    hipFree(h->chk_result);
+    if (h->chk_partials) hipFree(h->chk_partials);   // the result block lies behind the partials
     if (h->chk_host) hipHostFree(h->chk_host);
-    if (h->obs.ready) {
-        ObsBuffers& b = h->obs.b;
-        hipFree(b.rho);
-        hipFree(b.psi);
-        hipFree(b.j);
-        hipFree(b.F);
-        hipFree(b.u);
-        hipFree(b.partials);
-        hipFree(b.result);
-    }
+    if (h->obs.base) hipFree(h->obs.base);
     if (h->own_f) {
         hipFree(h->f[0]);
         hipFree(h->f[1]);
     }
     if (h->own_stream && h->stream) hipStreamDestroy(h->stream);
-    hipFree(h->solid);
+    if (h->solid) hipFree(h->solid);
     delete h;
 }
 
 static int ensure_obs(sc_lbm* h);
+static size_t obs_bytes(const sc_lbm* h);
+static void carve_obs(sc_lbm* h, void* base);
 static const void* args_ptr(sc_lbm* h);
 
 // Appends about `budget` evenly strided finite densities of one initial
@@ -631,8 +626,18 @@ static double* device_scratch(int dev)
     return g_scratch[dev];
 }
 
-extern "C" int sc_lbm_create(const sc_lbm_params* p, const double* rho_init, void* dev_a, void* dev_b,
-                             void* hip_stream, sc_lbm** out)
+// Set-up buffers that the items of a batch share, one after the other on its
+// stream: the initial density and the observation fields of the largest item.
+struct SetUp {
+    double* rho = nullptr;
+    void* obs = nullptr;
+};
+
+// sc_lbm_create, with the set-up buffers of a batch or (null) its own.  With
+// set-up buffers the work is left on the stream: the caller waits for it while
+// rho_init is still there.
+static int create_handle(const sc_lbm_params* p, const double* rho_init, void* dev_a, void* dev_b, void* hip_stream,
+                         const SetUp* shared, sc_lbm** out)
 {
     int rc = validate(p);
     if (rc != SC_OK) return rc;
@@ -703,20 +708,23 @@ extern "C" int sc_lbm_create(const sc_lbm_params* p, const double* rho_init, voi
     fill_args(h, h->af);
     fill_args(h, h->ad);
     // initial state from rho_init (or rho = 1)
-    double* rho_d = nullptr;
-    e = hipMalloc(&rho_d, sizeof(double) * h->n);
+    double* rho_d = shared ? shared->rho : nullptr;
+    e = shared ? hipSuccess : hipMalloc(&rho_d, sizeof(double) * h->n);
     if (e != hipSuccess) {
         rc = hip_err(e);
         release(h);
         return rc;
     }
+    auto drop_rho = [&] {
+        if (!shared) hipFree(rho_d);
+    };
     std::vector<double> ones;
     const double* src = rho_init;
     if (!src) {
         try {
             ones.assign(h->n, 1.0);
         } catch (const std::bad_alloc&) {
-            hipFree(rho_d);
+            drop_rho();
             release(h);
             return SC_E_NOMEM;
         }
@@ -731,9 +739,10 @@ extern "C" int sc_lbm_create(const sc_lbm_params* p, const double* rho_init, voi
     if (e == hipSuccess && p->init == SC_INIT_REST) {
         // F of psi(rho_init) from the equilibrium state just written, then
         // the populations again at the equilibrium of -F / (2 rho)
-        rc = ensure_obs(h);
+        if (shared) carve_obs(h, shared->obs);
+        else rc = ensure_obs(h);
         if (rc != SC_OK) {
-            hipFree(rho_d);
+            drop_rho();
             release(h);
             return rc;
         }
@@ -745,11 +754,12 @@ extern "C" int sc_lbm_create(const sc_lbm_params* p, const double* rho_init, voi
             e = launch_init_rest(p->lattice, h->f[0], p->precision, rho_d, b.F, p->nx, p->ny, p->nz,
                                  h->p.rho_ref, h->stream);
     }
-    if (e == hipSuccess) {
+    if (shared) h->obs.ready = false;   // the next item carves the same buffers
+    if (e == hipSuccess && (!shared || !rho_init)) {   // `ones` leaves scope
         where = "hipStreamSynchronize(create)";
         e = hipStreamSynchronize(h->stream);
     }
-    hipFree(rho_d);
+    drop_rho();
     if (e != hipSuccess) {
         rc = hip_err_at(e, where);
         release(h);
@@ -757,6 +767,12 @@ extern "C" int sc_lbm_create(const sc_lbm_params* p, const double* rho_init, voi
     }
     *out = h;
     return SC_OK;
+}
+
+extern "C" int sc_lbm_create(const sc_lbm_params* p, const double* rho_init, void* dev_a, void* dev_b,
+                             void* hip_stream, sc_lbm** out)
+{
+    return create_handle(p, rho_init, dev_a, dev_b, hip_stream, nullptr, out);
 }
 
 extern "C" void sc_lbm_destroy(sc_lbm* h)
@@ -881,16 +897,15 @@ static int ensure_check(sc_lbm* h)
 {
     if (h->chk_host) return SC_OK;
     const int nb = check_blocks(h->p.lattice, h->p.nx, h->p.ny, h->p.nz);
-    hipError_t e = hipMalloc(&h->chk_partials, sizeof(double) * kObsSlots * nb);
-    if (e == hipSuccess) e = hipMalloc(&h->chk_result, sizeof(double) * kCheckSlots);
+    hipError_t e = hipMalloc(&h->chk_partials, sizeof(double) * ((size_t)kObsSlots * nb + kCheckSlots));
     if (e == hipSuccess) e = hipHostMalloc(&h->chk_host, sizeof(double) * kCheckSlots, hipHostMallocDefault);
     if (e != hipSuccess) {
-        hipFree(h->chk_partials);
-        hipFree(h->chk_result);
-        h->chk_partials = h->chk_result = nullptr;
+        if (h->chk_partials) hipFree(h->chk_partials);
+        h->chk_partials = nullptr;
         h->chk_host = nullptr;
         return hip_err(e);
     }
+    h->chk_result = h->chk_partials + (size_t)kObsSlots * nb;
     return SC_OK;
 }
 
@@ -951,76 +966,45 @@ static hipError_t run_chunk(sc_lbm* h, int64_t K)
     return hipSuccess;
 }
 
+static int obs_blocks(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(1024, (n + 255) / 256)); }
+
+// bytes of a handle's observation buffers: rho, j, F and u, the partials and
+// the result in doubles, psi (8 bytes a node, of either precision) behind them
+static size_t obs_bytes(const sc_lbm* h)
+{
+    const size_t n = (size_t)h->n;
+    return sizeof(double) * (n * (2 + 3 * (size_t)h->dim) + (size_t)kObsSlots * obs_blocks(h->n) + kCheckSlots);
+}
+
+static void carve_obs(sc_lbm* h, void* base)
+{
+    ObsBuffers& b = h->obs.b;
+    const size_t n = (size_t)h->n, v = n * h->dim;
+    double* p = (double*)base;
+    b.nblk = obs_blocks(h->n);
+    b.rho = p;
+    b.j = b.rho + n;
+    b.F = b.j + v;
+    b.u = b.F + v;
+    b.partials = b.u + v;
+    b.result = b.partials + (size_t)kObsSlots * b.nblk;
+    b.psi = b.result + kCheckSlots;
+    h->obs.ready = true;
+}
+
 static int ensure_obs(sc_lbm* h)
 {
     if (h->obs.ready) return SC_OK;
-    ObsBuffers& b = h->obs.b;
-    const int64_t n = h->n;
-    b.nblk = (int)std::min<int64_t>(1024, (n + 255) / 256);
-    if (b.nblk < 1) b.nblk = 1;
-    hipError_t e = hipMalloc(&b.rho, sizeof(double) * n);
-    if (e == hipSuccess) e = hipMalloc(&b.psi, h->tsize * n);
-    if (e == hipSuccess) e = hipMalloc(&b.j, sizeof(double) * 3 * n);
-    if (e == hipSuccess) e = hipMalloc(&b.F, sizeof(double) * 3 * n);
-    if (e == hipSuccess) e = hipMalloc(&b.u, sizeof(double) * 3 * n);
-    if (e == hipSuccess) e = hipMalloc(&b.partials, sizeof(double) * kObsSlots * b.nblk);
-    if (e == hipSuccess) e = hipMalloc(&b.result, sizeof(double) * kObsSlots);
+    hipError_t e = hipMalloc(&h->obs.base, obs_bytes(h));
     if (e != hipSuccess) {
-        hipFree(b.rho);
-        hipFree(b.psi);
-        hipFree(b.j);
-        hipFree(b.F);
-        hipFree(b.u);
-        hipFree(b.partials);
-        hipFree(b.result);
-        b = ObsBuffers{};
+        h->obs.base = nullptr;
         return hip_err(e);
     }
-    h->obs.ready = true;
+    carve_obs(h, h->obs.base);
     return SC_OK;
 }
 
 static const void* args_ptr(sc_lbm* h) { return h->p.precision == SC_FP64 ? (const void*)&h->ad : (const void*)&h->af; }
-
-static void fill_obs(const sc_lbm* h, const double* res, double rin, double rout, double psi_in, double psi_out,
-                     sc_lbm_obs* o);
-
-// fields + reductions of the current state; fills obs (except convergence fields)
-static int observe_core(sc_lbm* h, sc_lbm_obs* o)
-{
-    int rc = ensure_obs(h);
-    if (rc != SC_OK) return rc;
-    ObsBuffers& b = h->obs.b;
-    const sc_lbm_params& p = h->p;
-    hipError_t e = launch_macro(p.lattice, p.precision, h->f[h->cur], args_ptr(h), b, h->stream);
-    if (e == hipSuccess) e = launch_force(h->dim, p.precision, p.order, args_ptr(h), b, true, h->stream);
-    if (e == hipSuccess) e = launch_reduce(h->dim, b, h->solid, h->n, h->stream);
-    double res[kObsSlots];
-    if (e == hipSuccess) e = hipMemcpyAsync(res, b.result, sizeof(res), hipMemcpyDeviceToHost, h->stream);
-    const int64_t ic = (int64_t)(p.nx / 2) + (int64_t)p.nx * ((int64_t)(p.ny / 2) + (int64_t)p.ny * (p.nz / 2));
-    double rin = 0, rout = 0;
-    double psi_pair[2] = {0, 0};
-    float psi_pair_f[2] = {0, 0};
-    if (e == hipSuccess) e = hipMemcpyAsync(&rin, b.rho + ic, sizeof(double), hipMemcpyDeviceToHost, h->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(&rout, b.rho, sizeof(double), hipMemcpyDeviceToHost, h->stream);
-    if (p.precision == SC_FP64) {
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(&psi_pair[0], (double*)b.psi + ic, 8, hipMemcpyDeviceToHost, h->stream);
-        if (e == hipSuccess) e = hipMemcpyAsync(&psi_pair[1], (double*)b.psi, 8, hipMemcpyDeviceToHost, h->stream);
-    } else {
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(&psi_pair_f[0], (float*)b.psi + ic, 4, hipMemcpyDeviceToHost, h->stream);
-        if (e == hipSuccess) e = hipMemcpyAsync(&psi_pair_f[1], (float*)b.psi, 4, hipMemcpyDeviceToHost, h->stream);
-    }
-    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-    if (e != hipSuccess) return hip_err(e);
-    if (p.precision != SC_FP64) {
-        psi_pair[0] = psi_pair_f[0];
-        psi_pair[1] = psi_pair_f[1];
-    }
-    fill_obs(h, res, rin, rout, psi_pair[0], psi_pair[1], o);
-    return SC_OK;
-}
 
 // sc_lbm_obs (all but converged_by) from the reduction slots and the
 // (rho, psi) pair at the centre node and node 0
@@ -1232,19 +1216,28 @@ extern "C" int sc_lbm_check_noalloc(sc_lbm* h, sc_lbm_obs* obs)
 extern "C" int sc_lbm_observe(sc_lbm* h, sc_lbm_obs* obs, double* rho_out, double* u_out, void* f_out)
 {
     if (!h) return SC_E_INVAL;
-    sc_lbm_obs o;
-    int rc = observe_core(h, &o);
+    int rc = ensure_obs(h);
     if (rc != SC_OK) return rc;
-    o.converged_by = h->conv_by;
     ObsBuffers& b = h->obs.b;
-    hipError_t e = hipSuccess;
-    if (rho_out) e = hipMemcpyAsync(rho_out, b.rho, sizeof(double) * h->n, hipMemcpyDeviceToHost, h->stream);
+    const sc_lbm_params& p = h->p;
+    const int64_t ic = (int64_t)(p.nx / 2) + (int64_t)p.nx * ((int64_t)(p.ny / 2) + (int64_t)p.ny * (p.nz / 2));
+    double res[kCheckSlots];
+    hipError_t e = launch_macro(p.lattice, p.precision, h->f[h->cur], args_ptr(h), b, h->stream);
+    if (e == hipSuccess) e = launch_force(h->dim, p.precision, p.order, args_ptr(h), b, true, h->stream);
+    if (e == hipSuccess) e = launch_reduce(h->dim, p.precision, b, h->solid, h->n, ic, h->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(res, b.result, sizeof(res), hipMemcpyDeviceToHost, h->stream);
+    if (e == hipSuccess && rho_out)
+        e = hipMemcpyAsync(rho_out, b.rho, sizeof(double) * h->n, hipMemcpyDeviceToHost, h->stream);
     if (e == hipSuccess && u_out)
         e = hipMemcpyAsync(u_out, b.u, sizeof(double) * h->dim * h->n, hipMemcpyDeviceToHost, h->stream);
     if (e == hipSuccess && f_out)
         e = hipMemcpyAsync(f_out, h->f[h->cur], h->tsize * h->q * h->n, hipMemcpyDeviceToHost, h->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+    const hipError_t es = hipStreamSynchronize(h->stream);   // also after an error: res leaves scope
+    if (e == hipSuccess) e = es;
     if (e != hipSuccess) return hip_err(e);
+    sc_lbm_obs o;
+    obs_from_check(h, res, &o);
+    o.converged_by = h->conv_by;
     if (obs) *obs = o;
     return o.nonfinite ? SC_E_NONFINITE : SC_OK;
 }
@@ -1363,6 +1356,7 @@ struct sc_lbm_batch {
     hipStream_t stream = nullptr;
     bool own_stream = false;
     std::vector<sc_lbm*> items;
+    void* obs = nullptr;    // observation buffers of the largest item, carved by one item at a time
     void* pool = nullptr;
     void* desc = nullptr;
     int2* work = nullptr;
@@ -1413,19 +1407,25 @@ static void batch_release(sc_lbm_batch* b)
 {
     if (!b) return;
     batch_drop_graphs(b);
-    hipFree(b->cwork);
-    hipFree(b->citems);
-    hipFree(b->cpartials);
-    hipFree(b->cresults);
+    for (void* m : {(void*)b->cwork, (void*)b->citems, (void*)b->cpartials, (void*)b->cresults, b->obs, b->pool, b->desc,
+                    (void*)b->work, (void*)b->work2})
+        if (m) hipFree(m);
     if (b->chost) hipHostFree(b->chost);
     for (sc_lbm* h : b->items)
         if (h) release(h);
-    hipFree(b->pool);
-    hipFree(b->desc);
-    hipFree(b->work);
-    hipFree(b->work2);
     if (b->own_stream && b->stream) hipStreamDestroy(b->stream);
     delete b;
+}
+
+// observation buffers that fit every item, of either precision
+static int batch_ensure_obs(sc_lbm_batch* b)
+{
+    if (b->obs) return SC_OK;
+    size_t most = 0;
+    for (const sc_lbm* h : b->items) most = std::max(most, obs_bytes(h));
+    const hipError_t e = hipMalloc(&b->obs, most);
+    if (e != hipSuccess) b->obs = nullptr;
+    return hip_err(e);
 }
 
 constexpr int kBatchStrip = 8;   // tile columns per strip of the two-step work list
@@ -1697,13 +1697,36 @@ extern "C" int sc_lbm_batch_create(const sc_lbm_params* items, int32_t n, const 
         batch_release(b);
         return rc;
     }
+    // set-up buffers for the largest item; freed once every item is initialised
+    int64_t nmax = 0;
+    bool rest = false;
+    for (int i = 0; i < n; ++i) {
+        nmax = std::max(nmax, (int64_t)items[i].nx * items[i].ny);
+        rest = rest || items[i].init == SC_INIT_REST;
+    }
+    SetUp set;
+    e = hipMalloc(&set.rho, sizeof(double) * (size_t)nmax);
+    if (e == hipSuccess && rest) {
+        sc_lbm big;
+        big.n = nmax;   // 2D, as every item
+        e = hipMalloc(&b->obs, obs_bytes(&big));
+        set.obs = b->obs;
+    }
+    if (e != hipSuccess) {
+        const int rc = hip_err(e);
+        if (set.rho) hipFree(set.rho);
+        batch_release(b);
+        return rc;
+    }
     std::vector<unsigned char> desc(batch_item_bytes(b->precision) * n);
     for (int i = 0; i < n; ++i) {
         char* base = (char*)b->pool + off[i];
         const size_t half = (sc_lbm_state_bytes(&items[i]) + 255) / 256 * 256;
         sc_lbm* h = nullptr;
-        int rc = sc_lbm_create(&its[i], rho_init ? rho_init[i] : nullptr, base, base + half, b->stream, &h);
+        int rc = create_handle(&its[i], rho_init ? rho_init[i] : nullptr, base, base + half, b->stream, &set, &h);
         if (rc != SC_OK) {
+            hipStreamSynchronize(b->stream);   // earlier items' copies read the caller's densities
+            hipFree(set.rho);
             batch_release(b);
             return rc;
         }
@@ -1716,7 +1739,9 @@ extern "C" int sc_lbm_batch_create(const sc_lbm_params* items, int32_t n, const 
     fill_args(b->items[0], b->cf);
     fill_args(b->items[0], b->cd);
     e = hipMemcpyAsync(b->desc, desc.data(), desc.size(), hipMemcpyHostToDevice, b->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
+    const hipError_t es = hipStreamSynchronize(b->stream);
+    if (e == hipSuccess) e = es;
+    hipFree(set.rho);
     int rc = hip_err(e);
     if (rc == SC_OK) rc = batch_rebuild_work(b);
     if (rc != SC_OK) {
@@ -1786,7 +1811,11 @@ extern "C" int sc_lbm_batch_observe(sc_lbm_batch* b, int32_t item, sc_lbm_obs* o
                                     double* u_out)
 {
     if (!b || item < 0 || item >= b->n) return SC_E_INVAL;
-    int rc = sc_lbm_observe(b->items[item], obs, rho_out, u_out, nullptr);
+    int rc = batch_ensure_obs(b);
+    if (rc != SC_OK) return rc;
+    carve_obs(b->items[item], b->obs);
+    rc = sc_lbm_observe(b->items[item], obs, rho_out, u_out, nullptr);
+    b->items[item]->obs.ready = false;
     if (obs) {
         obs->converged_by = b->conv_by[item] > 0 ? b->conv_by[item] : 0;
         if (b->conv_by[item] < 0) obs->status = SC_E_NONFINITE;
@@ -1808,22 +1837,6 @@ extern "C" int32_t sc_lbm_batch_active(sc_lbm_batch* b)
     int32_t k = 0;
     for (int v : b->active) k += v;
     return k;
-}
-
-// free a handle's observation buffers (sized for its state precision)
-static void drop_obs(sc_lbm* h)
-{
-    if (!h->obs.ready) return;
-    ObsBuffers& o = h->obs.b;
-    hipFree(o.rho);
-    hipFree(o.psi);
-    hipFree(o.j);
-    hipFree(o.F);
-    hipFree(o.u);
-    hipFree(o.partials);
-    hipFree(o.result);
-    o = ObsBuffers{};
-    h->obs.ready = false;
 }
 
 // Take the net momentum out of every widened item's state.  The step
@@ -1907,7 +1920,6 @@ extern "C" int sc_lbm_batch_promote(sc_lbm_batch* b)
         double* a1 = (double*)((char*)pool + off[i] + half[i]);
         e = launch_widen((const float*)h->f[h->cur], a0, (int64_t)h->q * h->n, b->stream);
         drop_graphs(h);
-        drop_obs(h);
         h->p.precision = SC_FP64;
         h->tsize = 8;
         h->f[0] = a0;
