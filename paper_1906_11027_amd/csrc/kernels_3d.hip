@@ -17,6 +17,7 @@
 #include <cstdint>
 
 #include "kernels.h"
+#pragma clang fp contract(fast)   // every shape advances one step: nothing to keep in line
 
 namespace sclbm {
 

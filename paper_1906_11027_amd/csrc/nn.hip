@@ -30,6 +30,7 @@
 
 #include "../../include/sc_lbm.h"
 #include "kernels.h"   // xcd_swizzle
+#pragma clang fp contract(fast)
 
 namespace sclbm {
 namespace nn {

@@ -163,11 +163,11 @@ __device__ __forceinline__ void collide_lat(T (&g)[L::Q], T drho, T Fx, T Fy, co
             const T cu = T(L::cx[b]) * ux + T(L::cy[b]) * uy;
             const T cF = T(L::cx[b]) * Fx + T(L::cy[b]) * Fy;
             const T w = T(L::w[b]);
-            const T S = w * (K0 + cu * (a1 * cu + a2 * cF));
+            const T S = K0 + cu * (a1 * cu + a2 * cF);   // times w below, fused with the sum
             const T A = w * (b1 * cu + b2 * cF);
             const T gp = g[b], gm = g[m];
-            const T np = gp + ((S + A) - om * gp);
-            const T nm = gm + ((S - A) - om * gm);
+            const T np = gp + ((w * S + A) - om * gp);
+            const T nm = gm + ((w * S - A) - om * gm);
             dm += (gp - np) + (gm - nm);
             g[b] = np;
             g[m] = nm;
@@ -193,11 +193,11 @@ __device__ __forceinline__ void collide_lat(T (&g)[L::Q], T drho, T Fx, T Fy, co
             const T cs = T(L::cx[b]) * sx + T(L::cy[b]) * sy;
             const T w = T(L::w[b]);
             const T q = omm1 * cv;
-            const T S = w * (K0 + rho * (T(ics2h) * (cs * cs + q * cv) - K1));
+            const T S = K0 + rho * (T(ics2h) * (cs * cs + q * cv) - K1);   // times w below
             const T A = (w * ri) * (cs + q);
             const T gp = g[b], gm = g[m];
-            const T np = gp + ((S + A) - om * gp);
-            const T nm = gm + ((S - A) - om * gm);
+            const T np = gp + ((w * S + A) - om * gp);
+            const T nm = gm + ((w * S - A) - om * gm);
             dm += (gp - np) + (gm - nm);
             g[b] = np;
             g[m] = nm;

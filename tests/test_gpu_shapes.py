@@ -61,3 +61,24 @@ def test_automatic_2d_shape(shape, lattice, order, prec):
     rho0 = droplet_rho(shape, 13, seed=5)
     edm = lattice != "D2Q9"
     _agree(rho0, lattice.replace("edm", ""), 5, prec, -1, 1, order=order, tau=0.9, forcing="edm" if edm else "guo")
+
+
+@pytest.mark.parametrize("lattice", ["D2Q9", "D2Q9edm", "D2Q13", "D2Q25"])
+@pytest.mark.parametrize("order", [4, 6, 8, 10])
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+def test_2d_steps_round_alike(lattice, order, prec):
+    """Every 2D launch shape, and a run cut into single steps, gives the same
+    bits: 7 steps are three two-step launches and one single step."""
+    rho0 = droplet_rho((60, 44), 13, seed=6)
+    kw = dict(order=order, tau=0.9, forcing="edm" if lattice != "D2Q9" else "guo", precision=prec)
+    lat = lattice.replace("edm", "")
+    one = Sim(rho0, lat, **kw)
+    for _ in range(7):
+        one.step(1)
+    want = one.state()
+    one.close()
+    for v in range(-1, B.sc_lbm_num_variants(B.make_params(lat, (60, 44), **kw))):
+        sim = Sim(rho0, lat, variant=v, **kw)
+        sim.step(7)
+        assert np.array_equal(sim.state(), want), (v, sim.variant)
+        sim.close()
