@@ -172,8 +172,8 @@ int sc_lbm_create(const sc_lbm_params* p, const double* rho_init, void* dev_a, v
                   void* hip_stream, sc_lbm** out);
 
 /* Advance the state (Sec. 2, Eq. (1), (3), (4): psi, force, collision and
- * pull streaming fused in one kernel per step, or per two steps for the
- * launch shapes that block two steps in time; see
+ * pull streaming fused in one kernel per step, or per two or four steps for
+ * the launch shapes that block steps in time; see
  * sc_lbm_steps_per_launch).
  *   max_steps  steps to run (>= 0);
  *   tol        0: run exactly max_steps, asynchronously (nothing is read
@@ -289,10 +289,10 @@ int sc_lbm_autotune(const sc_lbm_params* p, int32_t steps, int32_t* best_variant
 const char* sc_lbm_variant_name(const sc_lbm* h);
 int sc_lbm_num_variants(const sc_lbm_params* p);
 
-/* Time steps one kernel launch of the handle's launch shape advances: 1, or
- * 2 for the D2Q9 and any-lattice 2D shapes that fuse two steps per launch
- * (temporal blocking; sc_lbm_step still advances exactly the steps asked
- * for, and with walls every launch takes one step).  0 on NULL. */
+/* Time steps one kernel launch of the handle's launch shape advances: 1, or 2
+ * or 4 for the 2D shapes that fuse several steps per launch (temporal
+ * blocking; sc_lbm_step still advances exactly the steps asked for, with the
+ * same bits).  0 on NULL. */
 int sc_lbm_steps_per_launch(const sc_lbm* h);
 
 void sc_lbm_destroy(sc_lbm* h);

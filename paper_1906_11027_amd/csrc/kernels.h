@@ -391,6 +391,22 @@ __device__ __forceinline__ void collide_d3q19(T (&g)[19], T drho, T Fx, T Fy, T 
 
 #pragma clang fp contract(on)
 
+// LDS of a block on gfx950
+constexpr size_t kLdsBytes = 160 * 1024;
+
+// The steps that a TX x TY tile with one node per thread (tilek.h) takes per
+// launch: k, or half of it until the pulled region fits a block and the
+// post-collision copy the LDS.  R force radius, M lattice reach, Q velocities.
+constexpr int tile_steps_fit(int R, int M, int Q, size_t value, int tx, int ty, int k)
+{
+    for (; k > 1; k /= 2) {
+        const int hc = (k - 1) * (R + M), pn = (tx + 2 * (hc + R)) * (ty + 2 * (hc + R));
+        const size_t cn = (size_t)(tx + 2 * hc) * (ty + 2 * hc);
+        if (pn <= 1024 && value * ((size_t)pn + (size_t)Q * cn) <= kLdsBytes) break;
+    }
+    return k;
+}
+
 // ------------------------------------------------------------ launchers ----
 // Fused force + collide + pull-stream step.  `variant` picks a launch shape
 // (see kernels_2d.hip / kernels_3d.hip / wide2d.h); returns hipSuccess or an
@@ -400,7 +416,7 @@ hipError_t launch_step_d2q9(const StepArgs<double>& a, int order, int variant, h
 hipError_t launch_step_d3q19(const StepArgs<float>& a, int order, bool mrt, int variant, hipStream_t s);
 hipError_t launch_step_d3q19(const StepArgs<double>& a, int order, bool mrt, int variant, hipStream_t s);
 int num_variants_d2q9();
-int variant_steps_d2q9(int v);   // time steps one launch of the shape advances (1 or 2)
+int variant_steps_d2q9(int v, int order, size_t value);   // time steps one launch of the shape advances
 int num_variants_d3q19();
 const char* variant_name_d2q9(int v);
 const char* variant_name_d3q19(int v);
@@ -412,7 +428,10 @@ hipError_t launch_step_wide(int lattice, const StepArgs<float>& a, int order, bo
 hipError_t launch_step_wide(int lattice, const StepArgs<double>& a, int order, bool edm, int variant,
                             hipStream_t s);
 int num_variants_wide();
-int variant_steps_wide(int v);   // 1, or 2 for the shapes that block two steps in time
+// the same of the any-lattice shapes; walls: the shapes that block two steps in
+// time over several nodes a thread have no wall form
+int variant_steps_wide(int v, int lattice, int order, size_t value);
+bool variant_walls_wide(int v);
 const char* variant_name_wide(int v);
 // per-lattice instantiations (kernels_wide_q*.hip)
 hipError_t launch_wide_q9(const StepArgs<float>& a, int order, bool edm, int variant, hipStream_t s);

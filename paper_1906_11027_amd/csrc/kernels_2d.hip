@@ -13,6 +13,7 @@
 // Ragged tiles: out-of-grid threads still fill LDS with wrapped (valid)
 // psi and only skip the store, so any nx, ny >= 1 works.
 #include "tile2.h"
+#include "tilek.h"
 
 namespace sclbm {
 
@@ -244,6 +245,23 @@ k_d2q9_tile2(StepArgs<T> a, int nbx, int nby, int sw)
     d2q9_tile2_body<T, ORDER, TX, TY, NT, true>(a, bx * TX, by * TY, psi1, psi2, s1);
 }
 
+// the model of k_tile_steps
+struct GuoModel {
+    using L = D2Q9;
+    static constexpr int Q = 9, M = 1;
+    static constexpr int opposite(int b) { return b; }   // no walls in this family
+    template <typename T>
+    __device__ __forceinline__ static T sum(const T (&g)[9])
+    {
+        return sum9(g);
+    }
+    template <typename T>
+    __device__ __forceinline__ static void collide(T (&g)[9], T drho, T Fx, T Fy, const StepArgs<T>& a)
+    {
+        collide_d2q9_srt(g, drho, Fx, Fy, a);
+    }
+};
+
 // ------------------------------------------------------------ dispatch ----
 struct Shape2D {
     const char* name;
@@ -253,11 +271,23 @@ static const Shape2D kShapes2D[] = {
     {"march256h128"}, {"march256h128pf2"}, {"march512h128"}, {"march256h128pf3"}, {"march512h128pf2"},
     {"tile2x16x16"}, {"tile2x32x8"}, {"tile2x32x16"}, {"tile2x64x8"}, {"tile2x64x16"}, {"tile2x32x32"},
     {"tile2x32x8t512"}, {"tile2x32x8t1024"},
+    {"tileK4x8x8"}, {"tileK2x8x8"}, {"tileK2x16x8"}, {"tileK4x16x8"}, {"tileK2x16x16"},
 };
 constexpr int kNumShapes2D = sizeof(kShapes2D) / sizeof(kShapes2D[0]);
 
 int num_variants_d2q9() { return kNumShapes2D; }
-int variant_steps_d2q9(int v) { return (v >= 9 && v <= 16) ? 2 : 1; }
+int variant_steps_d2q9(int v, int order, size_t value)
+{
+    const int R = order == 4 ? 1 : (order == 10 ? 3 : 2);
+    switch (v) {
+    case 17: return tile_steps_fit(R, 1, 9, value, 8, 8, 4);
+    case 18: return tile_steps_fit(R, 1, 9, value, 8, 8, 2);
+    case 19: return tile_steps_fit(R, 1, 9, value, 16, 8, 2);
+    case 20: return tile_steps_fit(R, 1, 9, value, 16, 8, 4);
+    case 21: return tile_steps_fit(R, 1, 9, value, 16, 16, 2);
+    default: return v >= 9 ? 2 : 1;
+    }
+}
 const char* variant_name_d2q9(int v) { return (v >= 0 && v < kNumShapes2D) ? kShapes2D[v].name : "?"; }
 
 template <typename T, int ORDER, int TX, int TY, int RPT>
@@ -313,6 +343,13 @@ static hipError_t launch_order(const StepArgs<T>& a, int variant, hipStream_t s)
     // thread (the 256^2 grid has one 32 x 8 tile per CU)
     case 15: return launch_tile2<T, ORDER, 32, 8, 512>(a, s);
     case 16: return launch_tile2<T, ORDER, 32, 8, 1024>(a, s);
+    case 17: return launch_tile_steps<T, GuoModel, ORDER, false, 8, 8, 4>(a, s);
+    case 18: return launch_tile_steps<T, GuoModel, ORDER, false, 8, 8, 2>(a, s);
+    case 19: return launch_tile_steps<T, GuoModel, ORDER, false, 16, 8, 2>(a, s);
+    case 20: return launch_tile_steps<T, GuoModel, ORDER, false, 16, 8, 4>(a, s);
+    case 21: return launch_tile_steps<T, GuoModel, ORDER, false, 16, 16, 2>(a, s);
+    // One step with a thread per pulled node (16 x 16, 32 x 16, 64 x 8), which the
+    // wider lattices take, was behind the shapes above at every size here.
     // measured and dropped: 64 x 32 and 128 x 16 tiles with 1024 threads
     // (fewer halo nodes per tile node, but one block per CU); at 8192^2 the
     // tuner kept 64 x 16 (FP32) and 32 x 16 (FP64).  A 16 x 16 tile with

@@ -132,10 +132,24 @@ static const char* const kShapesWide[] = {"wide64x8r2",     "wide32x8r1",     "w
                                           "wide64x16r2",    "wide128x16r2",   "wide256x8r2",
                                           "wide2x32x8t256", "wide2x64x8t512", "wide2x64x16t1024",
                                           "wide2x128x8t1024", "wide2x64x8t1024", "wide2x64x12t768",
-                                          "wide2x64x12t1024", "wide2x64x16t768", "wide2x128x12t1024"};
+                                          "wide2x64x12t1024", "wide2x64x16t768", "wide2x128x12t1024",
+                                          "wideK4x8x8", "wideK2x8x8", "wideK2x16x8", "wideK4x16x8",
+                                          "wideK2x16x16", "wideK1x16x16", "wideK1x64x8"};
 int num_variants_wide() { return (int)(sizeof(kShapesWide) / sizeof(kShapesWide[0])); }
-// shapes 6.. advance two steps per launch (no walls)
-int variant_steps_wide(int v) { return v >= 6 ? 2 : 1; }
+int variant_steps_wide(int v, int lattice, int order, size_t value)
+{
+    const int R = order == 4 ? 1 : (order == 10 ? 3 : 2), M = lattice == SC_D2Q9 ? 1 : 2;
+    const int Q = lattice == SC_D2Q9 ? 9 : (lattice == SC_D2Q13 ? 13 : 25);
+    switch (v) {
+    case 15: return tile_steps_fit(R, M, Q, value, 8, 8, 4);
+    case 16: return tile_steps_fit(R, M, Q, value, 8, 8, 2);
+    case 17: return tile_steps_fit(R, M, Q, value, 16, 8, 2);
+    case 18: return tile_steps_fit(R, M, Q, value, 16, 8, 4);
+    case 19: return tile_steps_fit(R, M, Q, value, 16, 16, 2);
+    default: return v >= 6 && v <= 14 ? 2 : 1;
+    }
+}
+bool variant_walls_wide(int v) { return v < 6 || v > 14; }
 const char* variant_name_wide(int v) { return (v >= 0 && v < num_variants_wide()) ? kShapesWide[v] : "?"; }
 
 template <typename T>
@@ -246,13 +260,20 @@ extern "C" int sc_lbm_num_variants(const sc_lbm_params* p)
     return family_variants(family_of(*p));
 }
 
-// Time steps one launch of the handle's shape advances (the two-step D2Q9
-// shapes fuse two steps per launch).
+// The launch shape that the handle's steps take: its own, or one with a wall
+// form where it has walls.
+static int wall_shape(const sc_lbm_params& p, int64_t n);
+static int shape_of(const sc_lbm* h)
+{
+    return h->solid && !variant_walls_wide(h->variant) ? wall_shape(h->p, h->n) : h->variant;
+}
+
+// Time steps one launch of the handle's shape advances.
 static int steps_per_launch(const sc_lbm* h)
 {
     switch (handle_family(h)) {
-    case kFamD2Q9: return variant_steps_d2q9(h->variant);
-    case kFamWide: return h->solid ? 1 : variant_steps_wide(h->variant);
+    case kFamD2Q9: return variant_steps_d2q9(h->variant, h->p.order, h->tsize);
+    case kFamWide: return variant_steps_wide(shape_of(h), h->p.lattice, h->p.order, h->tsize);
     default: return 1;
     }
 }
@@ -387,7 +408,50 @@ static int64_t tiles_of(const sc_lbm_params& p, int tx, int ty)
 }
 static double overhang(const sc_lbm_params& p, int tx) { return (double)((p.nx + tx - 1) / tx * tx) / p.nx; }
 
-// D2Q9 with Guo forcing: the two-step tiles, which read and write the state
+// Tiles with one node per thread and K steps per launch, for grids that one
+// round of blocks covers: there a step costs the launch and a chain of
+// latencies, so the smallest tile that keeps to 256 blocks is taken, and four
+// steps where the halo of four fits a block (FP64 on the reach-2 lattices: two;
+// D2Q25 E4 60^2 3.30, four steps 3.93).  us per step against the shapes taken
+// before:
+//   8 x 8     60^2: D2Q9 E4 FP64 1.84 / 2.53, E8 FP32 1.86 / 2.33, EDM E8 FP32
+//             1.93 / 2.95; D2Q13 E6 FP64 2.94 / 4.9; D2Q25 E8 FP64 4.1 / 7.7
+//   16 x 8    200 x 100: D2Q9 E8 FP64 2.92 / 3.23; D2Q13 E8 FP32 2.87 / 3.96;
+//             D2Q25 E8 FP64 5.33 / 7.9
+//   16 x 16   256^2: D2Q9 E8 FP32 2.51 / 2.57; D2Q13 E6 FP64 4.41 / 5.50; D2Q25 E8
+//             FP32 4.49 / 5.53.  D2Q9 (Guo) in FP64 beyond E4 stays with 32 x 8
+//             (3.24, 16 x 16 3.41).
+// In FP32 the E4 tile of reach-1 lattices is light enough for two rounds of
+// four steps (256^2 1.94, 16 x 16 2.16), and two 16 x 16 tiles share a CU: up to
+// 512 of them D2Q9 (Guo) in FP32 or at E4 (320^2 E8 3.20 / 3.51) and, in FP64,
+// D2Q25 (320^2 E8 11.3 / 12.1; E10 one step at a time, 12.1 / 14.9).
+// Shape names by family; -1: none of them.
+enum SmallShape { kK4x8x8, kK2x8x8, kK2x16x8, kK4x16x8, kK2x16x16, kK1x16x16, kK1x64x8 };
+static int small_shape(const sc_lbm_params& p, bool wide)
+{
+    const int R = p.order == 4 ? 1 : (p.order == 10 ? 3 : 2), M = p.lattice == SC_D2Q9 ? 1 : 2;
+    const bool d = p.precision == SC_FP64;
+    const bool four = !d || M == 1;
+    auto four_fit = [&](int tx, int ty) {
+        return four && tile_steps_fit(R, M, lattice_q(p.lattice), d ? 8 : 4, tx, ty, 4) == 4;
+    };
+    const int64_t t16x8 = tiles_of(p, 16, 8), t16 = tiles_of(p, 16, 16);
+    if (tiles_of(p, 8, 8) <= 256) return four_fit(8, 8) ? kK4x8x8 : kK2x8x8;
+    if (t16x8 <= (!d && M == 1 && p.order == 4 ? 512 : 256) && four_fit(16, 8)) return kK4x16x8;
+    if (t16x8 <= 256) return kK2x16x8;
+    if (!wide) return t16 <= 512 && (!d || p.order == 4) ? kK2x16x16 : -1;
+    if (t16 <= 256) return kK2x16x16;
+    if (t16 <= 512 && d && p.lattice == SC_D2Q25) return p.order == 10 ? kK1x16x16 : kK2x16x16;
+    return -1;
+}
+
+// both copies of the state fit the last-level cache (256 MB)
+static bool cache_resident(const sc_lbm_params& p)
+{
+    return 2 * sc_lbm_state_bytes(&p) <= (size_t)1 << 28;
+}
+
+// D2Q9 with Guo forcing, larger grids: the two-step tiles, which read and write the state
 // once per two steps and halve the launches.  us per step, E8 unless marked,
 // against the one-step shapes that were taken before (tile32x8r1 below 2^20
 // nodes, tile64x16r4 from there).  The smallest tile that covers the grid with
@@ -401,17 +465,23 @@ static double overhang(const sc_lbm_params& p, int tx) { return (double)((p.nx +
 // (2048^2 48.9 / 63.5 for 64 x 16), except from 2^20 to 3 million nodes, where the
 // state half fits the last-level cache (1448^2: tile64x4r1 25.7, 32 x 32 28.3).
 // FP64 takes 32 x 16, two blocks per CU (2048^2
-// 72.4 / 130); at E10 the 32 x 16 tile's 90 KB allow one: 32 x 32, except below
-// 1.5 million nodes, where the state sits in the last-level cache and the one-step
-// tile32x8r1 is ahead (1001 x 777: 20.5, against 24.8 for the best two-step shape).
+// 72.4 / 130); at E10 the 32 x 16 tile's 90 KB allow one: 32 x 32, except while
+// both copies of the state fit the last-level cache, where the one-step
+// tile32x8r1 is ahead (1001 x 777: 20.5, against 24.8 for the best two-step shape;
+// 666 x 2953, just out of it, 80 / 58).  E4 takes the light 16 x 16 tiles with one
+// node per thread in the cache (1500 x 1100: FP64 23.5, the shapes above 32.5; FP32
+// 14.9 / 17.3; 2600 x 2100, out of it, FP64 114 / 98).
 static int auto_variant_d2q9(const sc_lbm_params& p, int64_t n)
 {
-    constexpr int kOne = 2, k64x4 = 3, k32x16 = 11, k64x16 = 13, k32x32 = 14, k32x8t1024 = 16;
-    const bool e10 = p.order == 10, cached = n >= (int64_t)1 << 20 && n < 3000000;
+    constexpr int kOne = 2, k64x4 = 3, k32x16 = 11, k64x16 = 13, k32x32 = 14, k32x8t1024 = 16, kK = 17;
+    const bool e10 = p.order == 10, cached = n >= (int64_t)1 << 20 && n < 3000000, d = p.precision == SC_FP64;
+    const int small = small_shape(p, false);
+    if (small >= 0) return kK + small;
     if (tiles_of(p, 32, 8) <= 256) return k32x8t1024;
+    if (p.order == 4 && cache_resident(p) && (d ? tiles_of(p, 64, 16) > 256 : n >= (int64_t)1 << 19)) return kK + kK2x16x16;
     if (tiles_of(p, 32, 16) <= 256) return k32x16;
-    if (p.precision != SC_FP64) return !e10 ? k64x16 : (cached ? k64x4 : k32x32);
-    if (e10) return tiles_of(p, 32, 32) <= 256 || n >= 1500000 ? k32x32 : kOne;
+    if (!d) return !e10 || tiles_of(p, 64, 16) <= 256 ? k64x16 : (cached ? k64x4 : k32x32);
+    if (e10) return tiles_of(p, 32, 32) <= 512 || !cache_resident(p) ? k32x32 : kOne;
     return tiles_of(p, 64, 16) <= 256 ? k64x16 : k32x16;
 }
 
@@ -437,74 +507,108 @@ static int two_step_height(const sc_lbm_params& p, int reach)
     return best;
 }
 
+// One step with a thread per pulled node, 16 x 16 or 64 x 8: ahead of the
+// one-step tiles that pull their halo ring one node at a time wherever the
+// halo collisions of two steps do not pay.  us per step, P-R psi and EDM:
+//   16 x 16  1001 x 777: D2Q13 E8 FP64 29.1 / 31.4, E10 FP32 19.0 / 20.6; D2Q9 E10
+//            FP64 21.9 / 24.7; 400^2 D2Q25 E10 FP64 16.5 / 19.5
+//   64 x 8   D2Q25 E8 FP32 1001 x 777 28.4 / 31.1, E10 800 x 600 19.2 / 25.0; FP64 E8
+//            1500 x 1100 159 / 182, 2600 x 2100 508 / 549
+// Two steps of 16 x 16 for the reach-1 E4 in the last-level cache (D2Q9 EDM FP64
+// 1500 x 1100 25.7 / 33.5).
+//
 // Any-lattice 2D kernels (P-R psi, EDM); us per step against the one-step
 // shapes taken before (wide32x8r1 below 2^20 nodes, wide128x16r2 or, D2Q25 in
 // FP64, wide64x8r2 from there).
-//   FP32 below 2^19 nodes: the two-step tile of two_step_height (256^2: D2Q9 E8
-//     3.12, D2Q13 E6 3.83 / 5.22, D2Q25 E8 5.46 / 6.71; 512^2 D2Q25 E8 9.5 / 13.6);
-//     at E10, whose halos are the widest, 32 x 8 where 64-wide columns hang over
-//     by a fifth (96 x 2511 D2Q13: 8.6 / 9.0, 64 x 12 10.0), one step where even
-//     those take many rounds (143 x 2827: 12.8, two steps 15.3);
+//   FP32 below 2^19 nodes: the two-step tile of two_step_height (512^2 D2Q25 E8
+//     9.5 / 13.6); at E10, whose halos are the widest, 32 x 8 where 64-wide columns
+//     hang over by a fifth (96 x 2511 D2Q13: 8.6 / 9.0, 64 x 12 10.0), one step where
+//     even those take many rounds (143 x 2827: 12.8, two steps 15.3);
 //   FP32 beyond: the tile with the smallest halo share that still leaves two
 //     blocks per CU (4096 x 3000: D2Q13 E6 64 x 12 166, D2Q25 E8 64 x 16 388 /
 //     535).  While the state sits in the last-level cache, D2Q25 from E6 (below
 //     1.5 million nodes) and D2Q13 E10 (3 million) run one step at a time: the
-//     halo collisions cost more than the pass saved (1001 x 777 D2Q25 E8: 31.1,
-//     two steps 34.7; 1151 x 2081 D2Q13 E10: 44.6, two steps 54.4);
+//     halo collisions cost more than the pass saved (1151 x 2081 D2Q13 E10: 44.6,
+//     two steps 54.4);
 //   FP64, D2Q9: as FP32 with the tiles that still fit;
-//   FP64, D2Q13: 64 x 8 or 64 x 12 while two rounds cover the grid (256^2 E6 5.6 /
-//     6.4; 832 x 215 E8 64 x 12 7.9 / 10.5; three rounds of 64 x 8, 220 x 1452:
-//     15.7, one step 14.0) and two steps again from 2^20 nodes (2623 x 508 E8: 54.1 / 55.4; 4096 x 3000 E6: 404 / 533);
+//   FP64, D2Q13: 64 x 8 or 64 x 12 while two rounds cover the grid (832 x 215 E8
+//     64 x 12 7.9 / 10.5), at E4 64 x 16 (800 x 600 15.2 / 19.4), and two steps
+//     again from 2^20 nodes (2623 x 508 E8: 54.1 / 55.4; 4096 x 3000 E6: 404 / 533);
 //   FP64, D2Q25: from E6 only 32 x 4 fits, one step is ahead (4096 x 3000 E8:
 //     1068, two steps 1336).
 static int auto_variant_wide(const sc_lbm_params& p, int64_t n)
 {
-    constexpr int k64x8r2 = 0, k32x8r1 = 1, k64x16r2 = 3, k128x16r2 = 4;                             // one step
-    constexpr int t32x8 = 6, t64x8 = 7, t64x16t1024 = 8, t64x8t1024 = 10, t64x12t768 = 11;           // two steps
-    const int E = p.order;
-    const int64_t t8 = tiles_of(p, 64, 8), t16 = tiles_of(p, 64, 16), rounds16 = (t16 + 255) / 256;
-    const int64_t t128 = tiles_of(p, 128, 16);
-    // 64-wide columns that hang over, or a last round of blocks mostly empty
-    const bool poor64 = overhang(p, 64) > 1.2 || t16 * 5 < rounds16 * 256 * 4;
+    constexpr int k64x8r2 = 0, k32x8r1 = 1, k64x16r2 = 3, k128x16r2 = 4;                     // one step
+    constexpr int t32x8 = 6, t64x8 = 7, t64x16t1024 = 8, t64x8t1024 = 10, t64x12t768 = 11;   // two steps
+    constexpr int kK = 15, one16 = kK + kK1x16x16, one64 = kK + kK1x64x8, two16 = kK + kK2x16x16;
+    const int E = p.order, small = small_shape(p, true);
+    if (small >= 0) return kK + small;
+    const int64_t t8 = tiles_of(p, 64, 8), t12 = tiles_of(p, 64, 12), t16 = tiles_of(p, 64, 16);
+    const int64_t rounds16 = (t16 + 255) / 256;
+    const bool wide64 = overhang(p, 64) > 1.2;   // 64-wide columns hang over
+    const bool cached = cache_resident(p), cached4 = E == 4 && p.lattice == SC_D2Q9 && cached;
+    const bool full16 = t16 * 5 >= rounds16 * 256 * 4;   // no mostly empty last round of 64 x 16
     if (p.precision != SC_FP64) {
         if (n < (int64_t)1 << 19) {
             if (p.lattice == SC_D2Q25 && E == 10 && t8 > 256)   // 64 x 16 does not fit
-                return tiles_of(p, 64, 12) <= 256 ? t64x12t768 : k64x16r2;
+                return t12 <= 256 ? t64x12t768 : (wide64 ? one16 : one64);
             if (p.lattice == SC_D2Q25 && E == 4 && t8 > 512) return t64x8;
-            if (E == 10 && overhang(p, 64) > 1.2 && t8 > 256) return t8 <= 768 ? t32x8 : k32x8r1;
+            if (E == 10 && wide64 && t8 > 256) return t8 <= 768 ? t32x8 : one16;
+            if (p.lattice == SC_D2Q25 && E > 4 && wide64 && t8 > 256) return one16;   // 69 x 2285 E6: 9.8, 64 x 12 13.0
             const int ty = two_step_height(p, p.lattice == SC_D2Q9 ? 1 : 2);
             return ty == 8 ? t64x8t1024 : (ty == 12 ? t64x12t768 : t64x16t1024);
         }
         if (p.lattice == SC_D2Q25) {
             if (E == 4) return t64x8;
-            if (n < 1500000) {
-                if (overhang(p, 128) > 1.15) return k64x16r2;
-                return t128 * 5 < (t128 + 255) / 256 * 256 * 4 && n < (int64_t)1 << 20 ? k32x8r1 : k128x16r2;
-            }
+            if (n < 1500000) return wide64 ? one16 : one64;
             return E == 10 ? t64x12t768 : t64x16t1024;
         }
+        if (cached4) return two16;
         if (p.lattice == SC_D2Q9) return E == 10 ? t64x12t768 : t64x16t1024;
-        if (E == 10) return n < 3000000 ? k128x16r2 : t64x8;
+        if (E == 10) return n < 3000000 ? one16 : t64x8;
         return E == 4 ? t64x16t1024 : t64x12t768;
     }
     if (p.lattice == SC_D2Q25) {
         if (E == 4) return t32x8;
-        if (n < (int64_t)1 << 17) return k32x8r1;
-        return n < (int64_t)1 << 20 ? (poor64 && n < (int64_t)1 << 19 ? k32x8r1 : k64x16r2) : k64x8r2;
+        if (E == 10) return n < (int64_t)1 << 19 ? one16 : (n < (int64_t)1 << 20 ? k64x16r2 : k64x8r2);
+        if (n < (int64_t)1 << 18) return one16;
+        if (n < (int64_t)1 << 19) return wide64 ? k32x8r1 : (full16 ? k64x16r2 : one16);   // 129 x 2795: 28.3, one16 31.6
+        return wide64 ? k64x8r2 : one64;
     }
     if (p.lattice == SC_D2Q9) {
         if (n < (int64_t)1 << 17 && t8 <= 256) return t64x8t1024;
+        if (E == 10 && t12 <= 256) return t64x12t768;   // 64 x 16 does not fit
         if (t16 <= 256) return t64x16t1024;
-        if (E == 10) return n < 1500000 ? k32x8r1 : t32x8;
+        if (cached4) return two16;
+        if (E == 10) return cached ? one16 : t32x8;
         return E == 4 || n < (int64_t)1 << 19 ? t32x8 : t64x8;
     }
-    const int64_t t12 = tiles_of(p, 64, 12);
     if (t8 <= 256) return t64x8t1024;
-    if (t12 <= (E == 10 ? 512 : 256)) return t64x12t768;
+    if (t12 <= 256) return t64x12t768;
+    if (E == 4 && t16 <= 512 && full16) return t64x16t1024;
     if (E < 10 && t8 <= 512) return t64x8t1024;
-    if (n < (int64_t)1 << 20) return k32x8r1;
+    if (n < (int64_t)1 << 20) return one16;
     if (E == 10 && n < 1500000) return k128x16r2;
     return E == 4 ? t32x8 : t64x12t768;
+}
+
+// The shape of steps with walls where the handle's own has no wall form: the
+// tiles with one node per thread, two steps of 16 x 16 while two blocks per CU
+// cover the grid (320^2: D2Q13 E8 FP32 5.27 us per step, one step 5.57,
+// wide32x8r1 7.10; FP64 beyond E4 one step, 7.80 / 8.72), on D2Q9 and at E4 four
+// (512^2 D2Q25 E4 FP64 20.8, one step 23.1), and one step from there
+// (512^2 D2Q25 E8 FP32 13.1 / 14.7); wide128x16r2 on large grids.
+static int wall_shape(const sc_lbm_params& p, int64_t n)
+{
+    constexpr int k128x16r2 = 4, kK = 15;
+    const int small = small_shape(p, true);
+    if (small >= 0) return kK + small;
+    if (n >= (int64_t)1 << 20) return k128x16r2;
+    const bool d = p.precision == SC_FP64, light = p.lattice == SC_D2Q9 || p.order == 4;
+    if (p.order == 4 && p.lattice == SC_D2Q9) return kK + kK2x16x16;
+    if (tiles_of(p, 16, 16) > (light ? 1024 : 512)) return kK + kK1x16x16;
+    if (d && (p.order == 10 || (p.lattice == SC_D2Q13 && p.order > 4))) return kK + kK1x16x16;
+    return kK + kK2x16x16;
 }
 
 // D3Q19: the persistent march with balanced segments, on 64 x 8 tiles in
@@ -800,13 +904,12 @@ static hipError_t launch_family(sc_lbm* h, const StepArgs<T>& a, bool single = f
     switch (handle_family(h)) {
     case kFamD2Q9:
         return launch_step_d2q9(
-            a, p.order, single && variant_steps_d2q9(h->variant) != 1 ? single_step_d2q9(h->n) : h->variant, h->stream);
+            a, p.order, single && steps_per_launch(h) != 1 ? single_step_d2q9(h->n) : h->variant, h->stream);
     case kFamD3Q19: return launch_step_d3q19(a, p.order, p.collision == SC_MRT, h->variant, h->stream);
     default: {
-        // the odd step of a two-step shape, and every step with walls, take a
-        // one-step shape of the same tiling scale
-        int v = h->variant;
-        if ((single || h->solid) && variant_steps_wide(v) != 1) v = h->n < ((int64_t)1 << 20) ? 1 : 4;
+        // a step that the shape's launches leave over takes a one-step shape
+        int v = shape_of(h);
+        if (single && steps_per_launch(h) != 1) v = h->n < ((int64_t)1 << 20) ? 15 + kK1x16x16 : 4;
         return launch_step_wide(p.lattice, a, p.order, p.forcing == SC_EDM, v, h->stream);
     }
     }
@@ -1325,7 +1428,7 @@ extern "C" int sc_lbm_set_walls(sc_lbm* h, const uint8_t* solid, double rho_w)
         if (now == family_of(h->p))
             h->variant = h->p.variant >= 0 ? h->p.variant : auto_variant(h->p, h->n);
         else
-            h->variant = h->n < ((int64_t)1 << 20) ? 1 : 4;   // wide32x8r1 / wide128x16r2
+            h->variant = wall_shape(h->p, h->n);
     }
     reset_convergence(h);
     return SC_OK;

@@ -22,7 +22,7 @@
 // arrived: g*_b = g_{-b} (standard bounce-back; the rest-weight shift is
 // symmetric, so it commutes with the reversal).
 #pragma once
-#include "kernels.h"
+#include "tilek.h"
 
 namespace sclbm {
 
@@ -352,29 +352,6 @@ struct WideTile2 {
     }
 };
 
-template <typename T, int ORDER>
-__device__ __forceinline__ void wide_force_at(const T* c, int LW, T gc0, T& Fx, T& Fy)
-{
-    using ST = Stencil<2, ORDER>;
-    T sx = T(0), sy = T(0), ax = T(0), ay = T(0);
-#pragma unroll
-    for (int p = 0; p < ST::NP; ++p) {
-        constexpr PairList P = ST::P;
-        const int ex = P.e[p][0], ey = P.e[p][1];
-        const T d = c[ey * LW + ex] - c[-ey * LW - ex];
-        if (ex) ax += T(ex) * d;
-        if (ey) ay += T(ey) * d;
-        if (P.shell_end(p)) {
-            sx += T(P.w[p]) * ax;
-            sy += T(P.w[p]) * ay;
-            ax = ay = T(0);
-        }
-    }
-    const T pref = -gc0 * c[0];
-    Fx = pref * sx;
-    Fy = pref * sy;
-}
-
 template <typename T, typename L, int ORDER, bool EDM, int TX, int TY, int NT>
 __global__ void __launch_bounds__(NT)
 k_wide_tile2(StepArgs<T> a, int nbx, int nby, int sw)
@@ -442,7 +419,7 @@ k_wide_tile2(StepArgs<T> a, int nbx, int nby, int sw)
             const int cx = lx - R, cy = ly - R;
             if (cx >= 0 && cx < C1W && cy >= 0 && cy < C1H) {
                 T Fx, Fy;
-                wide_force_at<T, ORDER>(psi1 + ly * P1W + lx, P1W, a.gc0, Fx, Fy);
+                tile_force_at<T, ORDER>(psi1 + ly * P1W + lx, P1W, a.gc0, Fx, Fy);
                 collide_lat<T, L, EDM>(g[q], TreeSum<0, Q>::of(g[q]), Fx, Fy, a);
 #pragma unroll
                 for (int b = 0; b < Q; ++b) {
@@ -480,7 +457,7 @@ k_wide_tile2(StepArgs<T> a, int nbx, int nby, int sw)
         T h[Q];
         pull_s1((ly + R) * P2W + lx + R, h);
         T Fx, Fy;
-        wide_force_at<T, ORDER>(psi2 + (ly + R) * P2W + lx + R, P2W, a.gc0, Fx, Fy);
+        tile_force_at<T, ORDER>(psi2 + (ly + R) * P2W + lx + R, P2W, a.gc0, Fx, Fy);
         collide_lat<T, L, EDM>(h, TreeSum<0, Q>::of(h), Fx, Fy, a);
         const int xr = x0 + lx, yr = y0 + ly;
         if (xr < nx && yr < ny) {
@@ -491,8 +468,23 @@ k_wide_tile2(StepArgs<T> a, int nbx, int nby, int sw)
     }
 }
 
-// LDS of a block on gfx950
-constexpr size_t kLdsBytes = 160 * 1024;
+// the model of k_tile_steps
+template <typename LAT, bool EDM>
+struct WideModel {
+    using L = LAT;
+    static constexpr int Q = L::Q, M = lattice_reach<L>();
+    static constexpr int opposite(int b) { return sclbm::opposite<L>(b); }
+    template <typename T>
+    __device__ __forceinline__ static T sum(const T (&g)[Q])
+    {
+        return TreeSum<0, Q>::of(g);
+    }
+    template <typename T>
+    __device__ __forceinline__ static void collide(T (&g)[Q], T drho, T Fx, T Fy, const StepArgs<T>& a)
+    {
+        collide_lat<T, L, EDM>(g, drho, Fx, Fy, a);
+    }
+};
 
 template <typename T, typename L, int ORDER, bool EDM, int TX, int TY, int NT>
 static hipError_t launch_wide_tile2(const StepArgs<T>& a, hipStream_t s)
@@ -569,6 +561,14 @@ static hipError_t launch_wide_shape(const StepArgs<T>& a, int variant, hipStream
     case 14:
         if constexpr (!WALLS) return launch_wide_tile2<T, L, ORDER, EDM, 128, 12, 1024>(a, s);
         return hipErrorInvalidValue;
+    // one node per thread, with walls too
+    case 15: return launch_tile_steps<T, WideModel<L, EDM>, ORDER, WALLS, 8, 8, 4>(a, s);
+    case 16: return launch_tile_steps<T, WideModel<L, EDM>, ORDER, WALLS, 8, 8, 2>(a, s);
+    case 17: return launch_tile_steps<T, WideModel<L, EDM>, ORDER, WALLS, 16, 8, 2>(a, s);
+    case 18: return launch_tile_steps<T, WideModel<L, EDM>, ORDER, WALLS, 16, 8, 4>(a, s);
+    case 19: return launch_tile_steps<T, WideModel<L, EDM>, ORDER, WALLS, 16, 16, 2>(a, s);
+    case 20: return launch_tile_steps<T, WideModel<L, EDM>, ORDER, WALLS, 16, 16, 1>(a, s);
+    case 21: return launch_tile_steps<T, WideModel<L, EDM>, ORDER, WALLS, 64, 8, 1>(a, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -1,8 +1,8 @@
 """Launch shapes chosen by a rule, against the plain shapes of the same step.
 
-The shapes do the same arithmetic on the same values, but the compiler may
-fuse multiply-adds differently per shape: after k steps the states agree to a
-few roundings of their largest value per step (2e-6 in FP32 and 1e-14 in FP64
+The shapes do the same arithmetic on the same values; on D3Q19 the compiler may
+fuse multiply-adds differently per shape, so there the states agree after k
+steps to a few roundings of their largest value per step (2e-6 in FP32 and 1e-14 in FP64
 relative to it over 6 steps)."""
 import numpy as np
 import pytest
@@ -82,3 +82,31 @@ def test_2d_steps_round_alike(lattice, order, prec):
         sim.step(7)
         assert np.array_equal(sim.state(), want), (v, sim.variant)
         sim.close()
+
+
+# one node per thread: grids narrower than the halo of four steps, one tile and
+# a node more, a ragged grid of many tiles
+@pytest.mark.parametrize("shape", [(3, 2), (1, 17), (9, 33), (75, 130)])
+@pytest.mark.parametrize("lattice", ["D2Q9", "D2Q9edm", "D2Q13", "D2Q25"])
+@pytest.mark.parametrize("walls", [False, True])
+@pytest.mark.parametrize("order,prec", [(4, "fp32"), (8, "fp64"), (10, "fp32")])
+def test_steps_per_launch_round_alike(shape, lattice, walls, order, prec):
+    """Shapes of one, two and four steps per launch, with and without walls:
+    7 steps at once give the bits of 7 single steps of the plain tile."""
+    rng = np.random.default_rng(7)
+    rho0 = 1.0 + 0.05 * rng.random(shape)
+    solid = (rng.random(shape) < 0.2).astype(np.uint8) if walls else None
+    kw = dict(order=order, tau=0.9, forcing="edm" if lattice != "D2Q9" else "guo", precision=prec)
+    lat = lattice.replace("edm", "")
+    states = []
+    count = B.sc_lbm_num_variants(B.make_params(lat, shape, **kw))
+    for v in [1, -1] + list(range(count)):
+        sim = Sim(rho0, lat, variant=v, **kw)
+        if walls:
+            sim.set_walls(solid, 0.8)
+        for k in [1] * 7 if not states else [7]:
+            sim.step(k)
+        states.append((sim.state(), v, sim.variant))
+        sim.close()
+    for state, v, name in states[1:]:
+        assert np.array_equal(state, states[0][0]), (v, name)
