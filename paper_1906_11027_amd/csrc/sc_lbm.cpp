@@ -134,7 +134,7 @@ static const char* const kShapesWide[] = {"wide64x8r2",     "wide32x8r1",     "w
                                           "wide2x128x8t1024", "wide2x64x8t1024", "wide2x64x12t768",
                                           "wide2x64x12t1024", "wide2x64x16t768", "wide2x128x12t1024",
                                           "wideK4x8x8", "wideK2x8x8", "wideK2x16x8", "wideK4x16x8",
-                                          "wideK2x16x16", "wideK1x16x16", "wideK1x64x8"};
+                                          "wideK2x16x16", "wideK1x16x16", "wideK1x64x8", "wide2x64x14t1024"};
 int num_variants_wide() { return (int)(sizeof(kShapesWide) / sizeof(kShapesWide[0])); }
 int variant_steps_wide(int v, int lattice, int order, size_t value)
 {
@@ -146,10 +146,10 @@ int variant_steps_wide(int v, int lattice, int order, size_t value)
     case 17: return tile_steps_fit(R, M, Q, value, 16, 8, 2);
     case 18: return tile_steps_fit(R, M, Q, value, 16, 8, 4);
     case 19: return tile_steps_fit(R, M, Q, value, 16, 16, 2);
-    default: return v >= 6 && v <= 14 ? 2 : 1;
+    default: return (v >= 6 && v <= 14) || v == 22 ? 2 : 1;
     }
 }
-bool variant_walls_wide(int v) { return v < 6 || v > 14; }
+bool variant_walls_wide(int v) { return v < 6 || (v > 14 && v != 22); }
 const char* variant_name_wide(int v) { return (v >= 0 && v < num_variants_wide()) ? kShapesWide[v] : "?"; }
 
 template <typename T>
@@ -539,7 +539,7 @@ static int two_step_height(const sc_lbm_params& p, int reach)
 static int auto_variant_wide(const sc_lbm_params& p, int64_t n)
 {
     constexpr int k64x8r2 = 0, k32x8r1 = 1, k64x16r2 = 3, k128x16r2 = 4;                     // one step
-    constexpr int t32x8 = 6, t64x8 = 7, t64x16t1024 = 8, t64x8t1024 = 10, t64x12t768 = 11;   // two steps
+    constexpr int t32x8 = 6, t64x8 = 7, t64x16t1024 = 8, t64x8t1024 = 10, t64x12t768 = 11, t64x14t1024 = 22;   // two steps
     constexpr int kK = 15, one16 = kK + kK1x16x16, one64 = kK + kK1x64x8, two16 = kK + kK2x16x16;
     const int E = p.order, small = small_shape(p, true);
     if (small >= 0) return kK + small;
@@ -561,7 +561,7 @@ static int auto_variant_wide(const sc_lbm_params& p, int64_t n)
         if (p.lattice == SC_D2Q25) {
             if (E == 4) return t64x8;
             if (n < 1500000) return wide64 ? one16 : one64;
-            return E == 10 ? t64x12t768 : t64x16t1024;
+            return E == 10 ? t64x14t1024 : t64x16t1024;   // E10 8192^2: 2548, 64 x 12 2899
         }
         if (cached4) return two16;
         if (p.lattice == SC_D2Q9) return E == 10 ? t64x12t768 : t64x16t1024;
