@@ -86,6 +86,7 @@ TRAFFIC_RATIO = {
     # space, which changed their register allocation; the any-lattice and
     # the single-grid D2Q9 two-step shapes and the FP64 D3Q19 marches
     # re-counted with their non-temporal stores)
+    ("d2q9_e8_256", "tileK2x16x16"): (0.674, 0.500),
     ("d2q9_e8_256", "tile2x32x8t1024"): (0.678, 0.500),
     ("d2q9_e8_256", "tile2x32x8t512"): (0.685, 0.500),
     ("d2q9_e8_256", "tile2x16x16"): (0.907, 0.557),
@@ -171,6 +172,10 @@ TRAFFIC_RATIO = {
     ("d3q19_mrt_e8_320_fp64", "pmarch64x8r1h32pf1"): (3.165, 1.902),
     ("d3q19_mrt_e8_320_fp64", "pmarch64x8r1h16pf1"): (3.165, 1.902),
     # the persistent 32 x 8 shapes share one grid: their mean
+    # the balanced marches
+    ("d3q19_mrt_e8_128", "pmarch64x8r1pf1"): (1.253, 1.000),
+    ("d3q19_mrt_e8_320", "pmarch64x8r1pf1"): (1.246, 1.000),
+    ("d3q19_mrt_e8_320_fp64", "pmarch32x8r1pf1"): (1.302, 1.000),
     ("d3q19_mrt_e8_320_fp64", "pmarch32x8r1h64pf1"): (1.341, 1.000),
     ("d3q19_mrt_e8_320_fp64", "pmarch32x8r1h32pf1"): (1.341, 1.000),
     ("d3q19_mrt_e8_320_fp64", "rl64x8h64w4"): (2.345, 1.000),
@@ -449,6 +454,8 @@ def cpu_baseline(name, target_s=15.0):
 def kernel_label(w, r):
     """The fused step kernel a workload's tuned shape runs."""
     t = "double" if w.get("precision") == "fp64" else "float"
+    if "tileK" in r["variant"] or r["variant"].startswith("wideK"):
+        return "k_tile_steps<%s, %s, %d, ...> (%s)" % (t, w["lattice"], w["order"], r["variant"])
     if w["lattice"] == "D2Q9":
         k = "k_d2q9_tile2" if r["steps_per_launch"] == 2 else "k_d2q9_tile"
         return "%s<%s, %d, ...> (%s)" % (k, t, w["order"], r["variant"])

@@ -6,9 +6,8 @@
 
 namespace sclbm {
 
-// Two time steps per launch (temporal blocking) for small, latency-bound
-// grids, where the launch itself costs as much as a step.  A block owns a
-// TX x TY tile and computes, with R the force-stencil radius:
+// Two time steps per launch (temporal blocking): the state is read and written
+// once per two steps, and a launch serves two.  A block owns a TX x TY tile and computes, with R the force-stencil radius:
 //   phase 1  psi at t+1 on the tile + (2R+1) halo: pull the 9 values of each
 //            node from the state (kept in registers), sum, psi -> LDS psi1;
 //   phase 2  step t -> t+1 on the tile + (R+1) halo, a sub-region of the
@@ -16,9 +15,11 @@ namespace sclbm {
 //   phase 3  psi at t+2 on the tile + R halo, pulling from s1 -> LDS psi2;
 //   phase 4  step t+1 -> t+2 on the tile: pull from s1, force from psi2,
 //            collide, store.
-// The halo nodes are recomputed by the neighbouring tiles (about 1.9x the
-// node updates at 16 x 16), so this shape pays off only where launches
-// dominate.  Every region is walked by a bounded loop over its node count;
+// The halo nodes are recomputed by the neighbouring tiles (first-step
+// collisions: 1.5x at 64 x 16, 1.9x at 16 x 16, E8).  At 8192^2 E8 FP32 (64 x 16) the
+// kernel is bound by its vector instructions, about 11,500 wave instructions per
+// tile at four cycles on four SIMDs, 1.2 of the launch's 1.3 ms: 0.648 ms per step, one-step tiles 1.12.
+// Every region is walked by a bounded loop over its node count;
 // nodes outside the grid are computed on wrapped coordinates and not stored.
 // LDS regions of the two-step tile (values of T): psi at t+1 on the tile +
 // (2R+1), the post-collision copy s1 of 9 planes on the tile + (R+1), psi at
