@@ -105,20 +105,8 @@ __device__ __forceinline__ void d2q9_tile_body(const StepArgs<T>& a, int x0, int
         const int ly = ty * RPT + k;
         const int yr = y0 + ly;
         const T* c = psi_s + (ly + R) * LW + tx + R;
-        T sx = T(0), sy = T(0), ax = T(0), ay = T(0);
-#pragma unroll
-        for (int p = 0; p < ST::NP; ++p) {
-            constexpr PairList P = ST::P;
-            const int ex = P.e[p][0], ey = P.e[p][1];
-            const T d = c[ey * LW + ex] - c[-ey * LW - ex];
-            if (ex) ax += T(ex) * d;
-            if (ey) ay += T(ey) * d;
-            if (P.shell_end(p)) {
-                sx += T(P.w[p]) * ax;
-                sy += T(P.w[p]) * ay;
-                ax = ay = T(0);
-            }
-        }
+        T sx, sy;
+        force_sums<T, ORDER>([&](int ex, int ey) { return c[ey * LW + ex]; }, sx, sy);
         const T pref = -a.gc0 * c[0];
         collide_d2q9_srt(g[k], dr[k], pref * sx, pref * sy, a);
         if (xin && yr < ny) {
@@ -204,20 +192,8 @@ k_d2q9_march(StepArgs<T> a, int H, int nbx)
                     int sl[2 * R + 1];
 #pragma unroll
                     for (int d = -R; d <= R; ++d) sl[d + R] = ((j - R + d) % NS) * NT + t;
-                    T sx = T(0), sy = T(0), ax = T(0), ay = T(0);
-#pragma unroll
-                    for (int p = 0; p < ST::NP; ++p) {
-                        constexpr PairList P = ST::P;
-                        const int ex = P.e[p][0], ey = P.e[p][1];
-                        const T d = psi_s[sl[R + ey] + ex] - psi_s[sl[R - ey] - ex];
-                        if (ex) ax += T(ex) * d;
-                        if (ey) ay += T(ey) * d;
-                        if (P.shell_end(p)) {
-                            sx += T(P.w[p]) * ax;
-                            sy += T(P.w[p]) * ay;
-                            ax = ay = T(0);
-                        }
-                    }
+                    T sx, sy;
+                    force_sums<T, ORDER>([&](int ex, int ey) { return psi_s[sl[R + ey] + ex]; }, sx, sy);
                     const T pref = -a.gc0 * psi_s[sl[R]];
                     const T drc = sum9(g[sc]);
                     collide_d2q9_srt(g[sc], drc, pref * sx, pref * sy, a);

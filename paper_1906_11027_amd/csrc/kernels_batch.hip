@@ -27,23 +27,7 @@ constexpr int kBTX = 32, kBTY = 8, kBRMAX = 3;
 template <typename T, int ORDER>
 __device__ __forceinline__ void batch_force(const T* c, int LW, T& sx, T& sy)
 {
-    using ST = Stencil<2, ORDER>;
-    sx = T(0);
-    sy = T(0);
-    T ax = T(0), ay = T(0);
-#pragma unroll
-    for (int p = 0; p < ST::NP; ++p) {
-        constexpr PairList P = ST::P;
-        const int ex = P.e[p][0], ey = P.e[p][1];
-        const T d = c[ey * LW + ex] - c[-ey * LW - ex];
-        if (ex) ax += T(ex) * d;
-        if (ey) ay += T(ey) * d;
-        if (P.shell_end(p)) {   // one weight per shell
-            sx += T(P.w[p]) * ax;
-            sy += T(P.w[p]) * ay;
-            ax = ay = T(0);
-        }
-    }
+    force_sums<T, ORDER>([&](int ex, int ey) { return c[ey * LW + ex]; }, sx, sy);
 }
 
 template <typename T>

@@ -124,6 +124,8 @@ struct PairList {
     int e[48][3];   // one vector per pair
     double w[48];   // w_hat of the pair's shell
     int s[48];      // shell index of the pair (pairs are listed shell by shell)
+    int f[48];      // 2 where every component of the pair's shell is even, else 1
+    bool first[48][3];   // no earlier pair of the shell has this component
 
     // true if pair p is the last of its shell: the kernels sum e (psi+ - psi-)
     // over a shell and multiply by its weight once
@@ -157,6 +159,16 @@ constexpr PairList make_pairs()
                     const int mx = ma > mb ? (ma > mc ? ma : mc) : (mb > mc ? mb : mc);
                     if (mx > p.r) p.r = mx;
                 }
+    }
+    for (int i = 0; i < p.n; ++i) {
+        p.f[i] = 2;
+        for (int d = 0; d < 3; ++d) p.first[i][d] = true;
+        for (int k = 0; k < p.n; ++k)
+            for (int d = 0; d < 3; ++d) {
+                if (p.s[k] != p.s[i]) continue;
+                if (p.e[k][d] % 2 != 0) p.f[i] = 1;
+                if (k < i && p.e[k][d] != 0) p.first[i][d] = false;
+            }
     }
     return p;
 }

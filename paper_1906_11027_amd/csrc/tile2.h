@@ -17,8 +17,8 @@ namespace sclbm {
 //            collide, store.
 // The halo nodes are recomputed by the neighbouring tiles (first-step
 // collisions: 1.5x at 64 x 16, 1.9x at 16 x 16, E8).  At 8192^2 E8 FP32 (64 x 16) the
-// kernel is bound by its vector instructions, about 11,500 wave instructions per
-// tile at four cycles on four SIMDs, 1.2 of the launch's 1.3 ms: 0.648 ms per step, one-step tiles 1.12.
+// kernel is bound by its vector instructions, about 11,000 wave instructions per
+// tile at four cycles on four SIMDs, 0.9 of the launch's time: 0.630 ms per step, one-step tiles 1.12.
 // Every region is walked by a bounded loop over its node count;
 // nodes outside the grid are computed on wrapped coordinates and not stored.
 // LDS regions of the two-step tile (values of T): psi at t+1 on the tile +
@@ -59,20 +59,8 @@ __device__ __forceinline__ void d2q9_tile2_body(const StepArgs<T>& a, int x0, in
         pull_d2q9(a.fin, n, xo, yo, g);
     };
     auto force_at = [&](const T* c, int LW, T& Fx, T& Fy) {
-        T sx = T(0), sy = T(0), ax = T(0), ay = T(0);
-#pragma unroll
-        for (int p = 0; p < ST::NP; ++p) {
-            constexpr PairList P = ST::P;
-            const int ex = P.e[p][0], ey = P.e[p][1];
-            const T d = c[ey * LW + ex] - c[-ey * LW - ex];
-            if (ex) ax += T(ex) * d;
-            if (ey) ay += T(ey) * d;
-            if (P.shell_end(p)) {
-                sx += T(P.w[p]) * ax;
-                sy += T(P.w[p]) * ay;
-                ax = ay = T(0);
-            }
-        }
+        T sx, sy;
+        force_sums<T, ORDER>([&](int ex, int ey) { return c[ey * LW + ex]; }, sx, sy);
         const T pref = -a.gc0 * c[0];
         Fx = pref * sx;
         Fy = pref * sy;

@@ -10,21 +10,8 @@ namespace sclbm {
 template <typename T, int ORDER>
 __device__ __forceinline__ void tile_force_at(const T* c, int LW, T gc0, T& Fx, T& Fy)
 {
-    using ST = Stencil<2, ORDER>;
-    T sx = T(0), sy = T(0), ax = T(0), ay = T(0);
-#pragma unroll
-    for (int p = 0; p < ST::NP; ++p) {
-        constexpr PairList P = ST::P;
-        const int ex = P.e[p][0], ey = P.e[p][1];
-        const T d = c[ey * LW + ex] - c[-ey * LW - ex];
-        if (ex) ax += T(ex) * d;
-        if (ey) ay += T(ey) * d;
-        if (P.shell_end(p)) {
-            sx += T(P.w[p]) * ax;
-            sy += T(P.w[p]) * ay;
-            ax = ay = T(0);
-        }
-    }
+    T sx, sy;
+    force_sums<T, ORDER>([&](int ex, int ey) { return c[ey * LW + ex]; }, sx, sy);
     const T pref = -gc0 * c[0];
     Fx = pref * sx;
     Fy = pref * sy;

@@ -291,20 +291,8 @@ k_wide_tile(StepArgs<T> a, int nbx, int nby, int sw)
     for (int k = 0; k < RPT; ++k) {
         const int ly = ty * RPT + k;
         const T* c = psi_s + (ly + R) * LW + tx + R;
-        T sx = T(0), sy = T(0), ax = T(0), ay = T(0);
-#pragma unroll
-        for (int p = 0; p < ST::NP; ++p) {
-            constexpr PairList P = ST::P;
-            const int ex = P.e[p][0], ey = P.e[p][1];
-            const T d = c[ey * LW + ex] - c[-ey * LW - ex];
-            if (ex) ax += T(ex) * d;
-            if (ey) ay += T(ey) * d;
-            if (P.shell_end(p)) {
-                sx += T(P.w[p]) * ax;
-                sy += T(P.w[p]) * ay;
-                ax = ay = T(0);
-            }
-        }
+        T sx, sy;
+        force_sums<T, ORDER>([&](int ex, int ey) { return c[ey * LW + ex]; }, sx, sy);
         const T pref = -a.gc0 * c[0];
         if (wall[k]) {
             T r[Q];
