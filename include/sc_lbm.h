@@ -327,7 +327,11 @@ int sc_lbm_batch_create(const sc_lbm_params* items, int32_t n, const double* con
  * max_steps, asynchronously.  tol > 0: every K = items[0].obs_every steps
  * each active item is reduced and leaves the work list when it meets the
  * steady-state rule of sc_lbm_step, or is quarantined when non-finite.
- * Returns when all items have left or max_steps are done. */
+ * A quarantined item keeps the field of that check; which of its nodes are
+ * finite hangs on the rounding of every step before, so it is the same from
+ * run to run but differs between precisions, between launch shapes that round
+ * differently (0, 1, and 2 and 3 alike) and between values of K that are odd
+ * and even.  Returns when all items have left or max_steps are done. */
 int sc_lbm_batch_step(sc_lbm_batch* b, int64_t max_steps, double tol, int64_t* steps_done);
 
 /* Observables and optional fields of one item (as sc_lbm_observe);

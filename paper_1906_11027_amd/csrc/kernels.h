@@ -15,8 +15,12 @@
 // expression, and not as each kernel's surroundings happen to allow: a step
 // then rounds the same in every launch shape, so a run gives the same bits
 // however it is cut into launches of one and two steps.  (D3Q19 advances one
-// step in every shape; it keeps the compiler's choice, worth 2% at 128^3.)
+// step in every shape; it keeps the compiler's choice, worth 2% at 128^3.)  The
+// batched sweep, the initial state and the observables keep the compiler's
+// choice too: they define SC_LBM_CONTRACT_FREELY.
+#ifndef SC_LBM_CONTRACT_FREELY
 #pragma clang fp contract(on)
+#endif
 
 namespace sclbm {
 
@@ -416,7 +420,9 @@ __device__ __forceinline__ void collide_d3q19(T (&g)[19], T drho, T Fx, T Fy, T 
     }
 }
 
+#ifndef SC_LBM_CONTRACT_FREELY
 #pragma clang fp contract(on)
+#endif
 
 // LDS of a block on gfx950
 constexpr size_t kLdsBytes = 160 * 1024;

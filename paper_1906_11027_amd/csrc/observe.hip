@@ -6,6 +6,7 @@
 // the state precision, reduce a wavefront with xor-shuffles, combine the
 // waves of a block through LDS, and sum the per-block partials in a second
 // single-block pass in a fixed order (deterministic for a given grid).
+#define SC_LBM_CONTRACT_FREELY
 #include "reduce.h"
 
 namespace sclbm {

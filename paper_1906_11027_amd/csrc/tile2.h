@@ -31,12 +31,27 @@ struct Tile2Lds {
     static constexpr int P2W = TX + 2 * R, P2H = TY + 2 * R, P2N = P2W * P2H;
 };
 
+// Force sums and collision of a node of a single grid (the batched sweep has
+// its own form).
+struct GridNode {
+    template <typename T, int ORDER>
+    __device__ __forceinline__ static void force(const T* c, int LW, T& sx, T& sy)
+    {
+        force_sums<T, ORDER>([&](int ex, int ey) { return c[ey * LW + ex]; }, sx, sy);
+    }
+    template <typename T>
+    __device__ __forceinline__ static void collide(T (&g)[9], T drho, T Fx, T Fy, const StepArgs<T>& a)
+    {
+        collide_d2q9_srt(g, drho, Fx, Fy, a);
+    }
+};
+
 // The two steps of one tile at origin (x0, y0); psi1, psi2 and s1 point to
 // LDS of at least the sizes of Tile2Lds<R, TX, TY>.  Every thread of the
 // NT-thread block calls it (barriers inside).  NTSTORE marks the output
 // stores non-temporal (the single-grid kernel; the batched sweep keeps
 // plain stores).
-template <typename T, int ORDER, int TX, int TY, int NT, bool NTSTORE = false>
+template <typename T, class Node, int ORDER, int TX, int TY, int NT, bool NTSTORE = false>
 __device__ __forceinline__ void d2q9_tile2_body(const StepArgs<T>& a, int x0, int y0, T* __restrict__ psi1,
                                                 T* __restrict__ psi2, T* __restrict__ s1)
 {
@@ -60,7 +75,7 @@ __device__ __forceinline__ void d2q9_tile2_body(const StepArgs<T>& a, int x0, in
     };
     auto force_at = [&](const T* c, int LW, T& Fx, T& Fy) {
         T sx, sy;
-        force_sums<T, ORDER>([&](int ex, int ey) { return c[ey * LW + ex]; }, sx, sy);
+        Node::template force<T, ORDER>(c, LW, sx, sy);
         const T pref = -a.gc0 * c[0];
         Fx = pref * sx;
         Fy = pref * sy;
@@ -116,7 +131,7 @@ __device__ __forceinline__ void d2q9_tile2_body(const StepArgs<T>& a, int x0, in
             if (cx >= 0 && cx < C1W && cy >= 0 && cy < C1H) {
                 T Fx, Fy;
                 force_at(psi1 + ly * P1W + lx, P1W, Fx, Fy);
-                collide_d2q9_srt(g[q], sum9(g[q]), Fx, Fy, a);
+                Node::collide(g[q], sum9(g[q]), Fx, Fy, a);
                 const int ci = cy * C1W + cx;
 #pragma unroll
                 for (int b = 0; b < 9; ++b) s1[b * C1N + ci] = g[q][b];
@@ -153,7 +168,7 @@ __device__ __forceinline__ void d2q9_tile2_body(const StepArgs<T>& a, int x0, in
         pull_s1(lx + HC, ly + HC, g);
         T Fx, Fy;
         force_at(psi2 + (ly + R) * P2W + lx + R, P2W, Fx, Fy);
-        collide_d2q9_srt(g, sum9(g), Fx, Fy, a);
+        Node::collide(g, sum9(g), Fx, Fy, a);
         const int xr = x0 + lx, yr = y0 + ly;
         if (xr < nx && yr < ny) {
             const uint32_t off = (uint32_t)yr * rowb + (uint32_t)xr * TS;
