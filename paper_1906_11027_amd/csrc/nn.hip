@@ -363,6 +363,17 @@ __device__ __forceinline__ int xcd_unswizzle(int L, int nb)
     return (m % q) * 8 + r + m / q;
 }
 
+// Orders the LDS accesses of a wave's lanes: what any lane did before it, every
+// lane sees after it.  The hardware runs a wave's LDS accesses in order, so this
+// costs no instruction; it keeps the compiler, which follows one lane at a time,
+// from exchanging a store and a load of different lanes' values.
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // ---- weight gradients --------------------------------------------------
 // gW_t[co][ci] = sum_p g[co][p] x[ci][p + d_t].  Partial row v sums the 16 x 16
 // tiles xcd_swizzle(v) + k nblk, k = 0, 1, ..., of all images; it is
@@ -412,6 +423,7 @@ struct PairStage {
     __device__ __forceinline__ void clear(int lane) const
     {
         for (int i = lane; i < kWPatch; i += 64) patch[i] = 0.f;
+        wave_lds_sync();
     }
     // channels that do not exist are read as channel 0
     __device__ __forceinline__ Tile tile(int at, int lane) const
@@ -472,14 +484,19 @@ struct PairStage {
     __device__ __forceinline__ float* xrow(int k, int i, int c) const { return patch + ((2 * k + i) * 16 + c) * kWXRow + 4; }
     __device__ __forceinline__ float* grow(int i, int c) const { return patch + 4 * 16 * kWXRow + (i * 16 + c) * kWGRow; }
 
+    // after the slot's last reads, and with the other lanes' values in place for
+    // the next; in a ragged tile the outer pixel falls on another lane's row store
     __device__ __forceinline__ void stage(const Raw& v, const Tile& t, int slot, int lane) const
     {
+        wave_lds_sync();
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             *(f32x4*)(xrow(slot, i, lane >> 2) + 4 * (lane & 3)) = shifted(v.x[i], t.sh);
             *(f32x4*)(grow(i, lane >> 2) + 4 * (lane & 3)) = shifted(v.g[i], t.sh);
         }
+        wave_lds_sync();
         xrow(slot, (lane >> 4) & 1, lane & 15)[lane & 32 ? t.width : -1] = v.o;
+        wave_lds_sync();
     }
     // whether gradient row i of pair s >= 1 counts
     __device__ __forceinline__ bool counts(const Tile& t, int s, int i) const
