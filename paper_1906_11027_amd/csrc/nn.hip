@@ -535,7 +535,7 @@ k_conv_bwd_w(const float* __restrict__ in, const float* __restrict__ gout, float
     f32x4 acc[9];
 #pragma unroll
     for (int t = 0; t < 9; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float bsum = 0.f;
+    float bsum[2] = {0.f, 0.f};   // the bias's running sums of the lane's two row pairs
     // every wave of the block takes the same number of tiles, so that all meet
     // the barrier; without a tile of its own it adds zeros
     // Pair s goes through raw[s mod 3], its loads two pairs ahead: one wave per
@@ -563,6 +563,31 @@ k_conv_bwd_w(const float* __restrict__ in, const float* __restrict__ gout, float
                 d[j][dx] = ci_ok ? v : 0.f;
             }
     };
+    // The bias sums a pair's 32 pixels one after the other, then the row's tiles:
+    // chains that keep a sum of 10^5 values to a few 1e-10 of their magnitudes.
+    // The lanes of quarter kq keep pairs 1 + kq and 5 + kq as they pass, so four
+    // pairs are summed side by side (one pair at a time: 111 us for 5 -> 32).
+    f32x4 hold[2][4];
+    auto hold_g = [&](int s) {
+        if (kq == ((s - 1) & 3))
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) hold[i][j] = *(const f32x4*)(st.grow(i, r16) + 4 * j);
+    };
+    auto sum_g = [&](int half) {
+        float sum = 0.f;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const bool row = st.counts(t, 4 * half + kq + 1, i);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    sum += row && (EDGE == kEdgeNone || 4 * j + e < t.width) ? hold[i][j][e] : 0.f;
+        }
+        bsum[half] += sum;
+    };
     for (int wi = L0; wi < st.nwork + grp; wi += nblk) {
         __builtin_amdgcn_s_barrier();
         st.stage(raw[0], t, 0, lane);
@@ -573,6 +598,7 @@ k_conv_bwd_w(const float* __restrict__ in, const float* __restrict__ gout, float
         raw[1] = st.load(t, 4, lane);
         take_x(2, xw[2]);
         take_g(0, g[0]);
+        hold_g(1);
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             float xn[4][3];
@@ -582,7 +608,9 @@ k_conv_bwd_w(const float* __restrict__ in, const float* __restrict__ gout, float
                     const int s = (r + 3) / 2;
                     st.stage(raw[s % 3], t, s & 1, lane);
                     raw[s % 3] = s < 6 ? st.load(t, s + 3, lane) : st.load(nxt, s - 6, lane);
+                    hold_g(s);
                 }
+                if (r == 6 || r == 14) sum_g(r / 8);
                 take_x(r + 3, xn);
                 take_g(r + 1, g[(r + 1) & 1]);
             }
@@ -595,11 +623,9 @@ k_conv_bwd_w(const float* __restrict__ in, const float* __restrict__ gout, float
                         acc[3 * dy + dx] = __builtin_amdgcn_mfma_f32_16x16x4f32(g[r & 1][j], xw[(r + dy) % 3][j][dx],
                                                                                 acc[3 * dy + dx], 0, 0, 0);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                bsum += g[r & 1][j];
+            for (int j = 0; j < 4; ++j)
 #pragma unroll
                 for (int dx = 0; dx < 3; ++dx) xw[r % 3][j][dx] = r < 15 ? xn[j][dx] : 0.f;
-            }
             __builtin_amdgcn_sched_barrier(0);
         }
         t = nxt;
@@ -615,10 +641,13 @@ k_conv_bwd_w(const float* __restrict__ in, const float* __restrict__ gout, float
 #pragma unroll
             for (int t = 0; t < 9; ++t) pb[(ci * cout + co) * 9 + t] = acc[t][i];
     }
-    // bias: the four pixel classes of a channel
-    bsum += __shfl_xor(bsum, 16, 64);
-    bsum += __shfl_xor(bsum, 32, 64);
-    if (nt == 0 && kq == 0 && co_ok) pb[E + mt * 16 + r16] = bsum;
+    // bias: pairs 1 and 2, 3 and 4, ... of a channel, as a tree
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        bsum[k] += __shfl_xor(bsum[k], 16, 64);
+        bsum[k] += __shfl_xor(bsum[k], 32, 64);
+    }
+    if (nt == 0 && kq == 0 && co_ok) pb[E + mt * 16 + r16] = bsum[0] + bsum[1];
 }
 
 // The 32 -> 32 weight gradient on bf16 MFMAs: both operands split exactly into
