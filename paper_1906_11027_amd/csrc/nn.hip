@@ -553,14 +553,17 @@ k_conv_bwd_w(const float* __restrict__ in, const float* __restrict__ gout, float
             d[j] = row && (EDGE == kEdgeNone || 4 * j + kq < t.width) ? v : 0.f;
         }
     };
+    // without a tile of its own the wave has a copy of the last one: its pixels must
+    // not meet the zero gradients, an infinite one would give NaN
     auto take_x = [&](int q, float (&d)[4][3]) {
+        const bool ok = ci_ok && t.live;
         const float* x = st.xrow((q >> 1) & 1, q & 1, r16) + kq - 1;
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
             for (int dx = 0; dx < 3; ++dx) {
                 const float v = x[4 * j + dx];
-                d[j][dx] = ci_ok ? v : 0.f;
+                d[j][dx] = ok ? v : 0.f;
             }
     };
     // The bias sums a pair's 32 pixels one after the other, then the row's tiles:
