@@ -281,7 +281,9 @@ double sc_lbm_rho_ref(const sc_lbm* h);
  * choices persist across processes.  Outputs are nullable. */
 int sc_lbm_autotune(const sc_lbm_params* p, int32_t steps, int32_t* best_variant, double* best_ms_per_step);
 
-/* Name of the launch shape in use, and the number of launch shapes of the
+/* Name of the launch shape in use (with walls the one that their steps take;
+ * the number behind "K" is the most steps per launch, halved where the stencil's
+ * halo does not fit: sc_lbm_steps_per_launch tells), and the number of launch shapes of the
  * kernel family that serves *p (for sweeps through sc_lbm_params.variant;
  * *p's own variant field is ignored): D2Q9 with Guo forcing, D3Q19, and the
  * any-lattice 2D family (D2Q13, D2Q25, D2Q9 with EDM) each have their own

@@ -286,7 +286,7 @@ extern "C" const char* sc_lbm_variant_name(const sc_lbm* h)
     switch (handle_family(h)) {
     case kFamD2Q9: return variant_name_d2q9(h->variant);
     case kFamD3Q19: return variant_name_d3q19(h->variant);
-    default: return variant_name_wide(h->variant);
+    default: return variant_name_wide(shape_of(h));
     }
 }
 
