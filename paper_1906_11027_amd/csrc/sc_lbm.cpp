@@ -592,18 +592,32 @@ static int auto_variant_wide(const sc_lbm_params& p, int64_t n)
     return E == 4 ? t32x8 : t64x12t768;
 }
 
+// One step at a time on the any-lattice kernels, for steps that a shape's launches
+// leave over and for walls on large grids: 16 x 16 with one node per thread below
+// 2^20 nodes, wide128x16r2 from there, except for D2Q25 in FP64, whose step spills
+// in blocks of 1024 threads (up to 400 bytes a lane) and takes 64 x 8.  us per step with
+// walls, wide128x16r2 / wide64x8r2 / 64 x 8 with one node per thread: 1024^2 E4 167 /
+// 102 / 101, E8 189 / 116 / 100; 2600 x 2100 E4 813 / 532 / 489, E10 834 / 594 / 630.
+static int one_step_wide(const sc_lbm_params& p, int64_t n)
+{
+    constexpr int k64x8r2 = 0, k128x16r2 = 4, kK = 15;
+    if (n < (int64_t)1 << 20) return kK + kK1x16x16;
+    if (p.precision != SC_FP64 || p.lattice != SC_D2Q25) return k128x16r2;
+    return p.order == 10 || overhang(p, 64) > 1.2 ? k64x8r2 : kK + kK1x64x8;
+}
+
 // The shape of steps with walls where the handle's own has no wall form: the
 // tiles with one node per thread, two steps of 16 x 16 while two blocks per CU
 // cover the grid (320^2: D2Q13 E8 FP32 5.27 us per step, one step 5.57,
 // wide32x8r1 7.10; FP64 beyond E4 one step, 7.80 / 8.72), on D2Q9 and at E4 four
 // (512^2 D2Q25 E4 FP64 20.8, one step 23.1), and one step from there
-// (512^2 D2Q25 E8 FP32 13.1 / 14.7); wide128x16r2 on large grids.
+// (512^2 D2Q25 E8 FP32 13.1 / 14.7), on large grids one_step_wide()'s.
 static int wall_shape(const sc_lbm_params& p, int64_t n)
 {
-    constexpr int k128x16r2 = 4, kK = 15;
+    constexpr int kK = 15;
     const int small = small_shape(p, true);
     if (small >= 0) return kK + small;
-    if (n >= (int64_t)1 << 20) return k128x16r2;
+    if (n >= (int64_t)1 << 20) return one_step_wide(p, n);
     const bool d = p.precision == SC_FP64, light = p.lattice == SC_D2Q9 || p.order == 4;
     if (p.order == 4 && p.lattice == SC_D2Q9) return kK + kK2x16x16;
     if (tiles_of(p, 16, 16) > (light ? 1024 : 512)) return kK + kK1x16x16;
@@ -909,7 +923,7 @@ static hipError_t launch_family(sc_lbm* h, const StepArgs<T>& a, bool single = f
     default: {
         // a step that the shape's launches leave over takes a one-step shape
         int v = shape_of(h);
-        if (single && steps_per_launch(h) != 1) v = h->n < ((int64_t)1 << 20) ? 15 + kK1x16x16 : 4;
+        if (single && steps_per_launch(h) != 1) v = one_step_wide(p, h->n);
         return launch_step_wide(p.lattice, a, p.order, p.forcing == SC_EDM, v, h->stream);
     }
     }

@@ -38,3 +38,23 @@ def test_name_and_steps_describe_one_shape(shape, prec):
         sim.set_walls(None, 0.0)
         assert (sim.variant, sim.steps_per_launch) == (name, steps)
         sim.close()
+
+
+@pytest.mark.parametrize("order", [4, 6, 8, 10])
+def test_large_d2q25_fp64_does_not_spill(order):
+    """From 2^20 nodes D2Q25 in FP64 steps on 512-thread or one-node tiles, with
+    walls too: the 1,024-thread blocks of wide128x16r2 spill its 25 values.  An odd
+    step more than the launches take gives the bits of single steps."""
+    shape = (1030, 1024)
+    rho0 = 1.0 + 0.05 * np.random.default_rng(3).random(shape)
+    kw = dict(order=order, tau=0.9, forcing="edm", precision="fp64")
+    sim = Sim(rho0, "D2Q25", **kw)
+    sim.set_walls(_channel(shape), 1.0)
+    assert sim.variant in ("wide64x8r2", "wideK1x64x8"), sim.variant
+    sim.set_walls(None, 0.0)
+    one = Sim(rho0, "D2Q25", variant=1, **kw)
+    sim.step(3)
+    one.step(3)
+    assert np.array_equal(sim.state(), one.state())
+    sim.close()
+    one.close()
