@@ -485,6 +485,10 @@ static int auto_variant_d2q9(const sc_lbm_params& p, int64_t n)
     return tiles_of(p, 64, 16) <= 256 ? k64x16 : k32x16;
 }
 
+// single-step D2Q9 shape used for the odd step of a two-step shape:
+// tile32x8r1, or tile64x16r4 on large grids (2048^2 E8 FP32: 76 us against 93)
+static int single_step_d2q9(int64_t n) { return n < ((int64_t)1 << 20) ? 2 : 0; }
+
 // Two-step tiles 64 x 8, 64 x 12 and 64 x 16 (all of 768 or 1024 threads) on a
 // grid that a few rounds of blocks cover: a launch takes about rounds x the
 // nodes a tile pulls, (64 + 2 H)(TY + 2 H) with H = 2R + M, so the tile with
@@ -645,14 +649,20 @@ static int auto_variant_3d(const sc_lbm_params& p)
     return k64;
 }
 
+// Strips of at most 32 columns and 2^25 rows or more: a launch holds fewer than
+// 2^32 threads a dimension, which one-dimensional blocks of up to 1024 threads on 64 x
+// 8 nodes use up where most of a tile hangs over.  (Full columns reach the 2^32
+// bytes of a velocity plane first.)  The one-step shapes' blocks count 64 or 128.
+static bool long_strip(const sc_lbm_params& p) { return tiles_of(p, 64, 8) >= (int64_t)1 << 22; }
+
 static int auto_variant(const sc_lbm_params& p, int64_t n)
 {
     const int tuned = tune_lookup(p);
     if (tuned >= 0) return tuned;
     switch (family_of(p)) {
-    case kFamD2Q9: return auto_variant_d2q9(p, n);
+    case kFamD2Q9: return long_strip(p) ? single_step_d2q9(n) : auto_variant_d2q9(p, n);
     case kFamD3Q19: return auto_variant_3d(p);
-    default: return auto_variant_wide(p, n);
+    default: return long_strip(p) ? one_step_wide(p, n) : auto_variant_wide(p, n);
     }
 }
 
@@ -906,10 +916,6 @@ extern "C" void* sc_lbm_stream(sc_lbm* h) { return h ? (void*)h->stream : nullpt
 
 extern "C" double sc_lbm_rho_ref(const sc_lbm* h) { return h ? h->p.rho_ref : std::nan(""); }
 
-
-// single-step D2Q9 shape used for the odd step of a two-step shape:
-// tile32x8r1, or tile64x16r4 on large grids (2048^2 E8 FP32: 76 us against 93)
-static int single_step_d2q9(int64_t n) { return n < ((int64_t)1 << 20) ? 2 : 0; }
 
 template <typename T>
 static hipError_t launch_family(sc_lbm* h, const StepArgs<T>& a, bool single = false)
