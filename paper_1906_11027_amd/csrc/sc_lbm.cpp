@@ -466,9 +466,11 @@ static bool cache_resident(const sc_lbm_params& p)
 // state half fits the last-level cache (1448^2: tile64x4r1 25.7, 32 x 32 28.3).
 // FP64 takes 32 x 16, two blocks per CU (2048^2
 // 72.4 / 130); at E10 the 32 x 16 tile's 90 KB allow one: 32 x 32, except while
-// both copies of the state fit the last-level cache, where the one-step
-// tile32x8r1 is ahead (1001 x 777: 20.5, against 24.8 for the best two-step shape;
-// 666 x 2953, just out of it, 80 / 58).  E4 takes the light 16 x 16 tiles with one
+// both copies of the state fit the last-level cache and the tiles leave most of
+// their last round of 256 empty, where the one-step tile32x8r1 is ahead (529^2, 289
+// tiles: 12.0, 32 x 32 13.8; 565^2, 324: 12.4 / 14.3; 632^2, 400: 14.6 / 14.1; 1248 x
+// 416, 507: 16.7 / 15.1; 1001 x 777: 20.5, against 24.8 for the best two-step
+// shape; 666 x 2953, just out of the cache, 80 / 58).  E4 takes the light 16 x 16 tiles with one
 // node per thread in the cache (1500 x 1100: FP64 23.5, the shapes above 32.5; FP32
 // 14.9 / 17.3; 2600 x 2100, out of it, FP64 114 / 98).
 static int auto_variant_d2q9(const sc_lbm_params& p, int64_t n)
@@ -481,7 +483,10 @@ static int auto_variant_d2q9(const sc_lbm_params& p, int64_t n)
     if (p.order == 4 && cache_resident(p) && (d ? tiles_of(p, 64, 16) > 256 : n >= (int64_t)1 << 19)) return kK + kK2x16x16;
     if (tiles_of(p, 32, 16) <= 256) return k32x16;
     if (!d) return !e10 || tiles_of(p, 64, 16) <= 256 ? k64x16 : (cached ? k64x4 : k32x32);
-    if (e10) return tiles_of(p, 32, 32) <= 512 || !cache_resident(p) ? k32x32 : kOne;
+    if (e10) {
+        const int64_t t = tiles_of(p, 32, 32);
+        return t <= 256 || (t >= 400 && t <= 512) || !cache_resident(p) ? k32x32 : kOne;
+    }
     return tiles_of(p, 64, 16) <= 256 ? k64x16 : k32x16;
 }
 

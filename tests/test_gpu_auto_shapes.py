@@ -1,0 +1,24 @@
+"""Lines of the automatic 2D launch shapes where both sides were measured (the
+figures stand at the rules in sc_lbm.cpp): the shape on either side of each."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():  # pragma: no cover
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_1906_11027_amd import sc_lbm as B  # noqa: E402
+
+
+@pytest.mark.parametrize("lattice,forcing,prec,order,shape,name", [
+    # E10 in FP64: a mostly empty last round of 32 x 32 tiles goes to one step
+    ("D2Q9", "guo", "fp64", 10, (504, 504), "tile2x32x32"), ("D2Q9", "guo", "fp64", 10, (529, 529), "tile32x8r1"),
+    ("D2Q9", "guo", "fp64", 10, (567, 493), "tile32x8r1"), ("D2Q9", "guo", "fp64", 10, (640, 640), "tile2x32x32"),
+    ("D2Q9", "guo", "fp64", 10, (721, 721), "tile32x8r1"), ("D2Q9", "guo", "fp64", 10, (2048, 2048), "tile2x32x32"),
+])
+def test_shape(lattice, forcing, prec, order, shape, name):
+    h = B.sc_lbm_create(B.make_params(lattice, shape, order=order, precision=prec, forcing=forcing, tau=0.9))
+    try:
+        assert B.sc_lbm_variant_name(h) == name
+    finally:
+        B.sc_lbm_destroy(h)
