@@ -459,12 +459,11 @@ static bool cache_resident(const sc_lbm_params& p)
 // much as the first:
 //   32 x 8 tiles with 1024 threads (256^2: FP32 2.57 / 3.64, FP64 3.34 / 4.62);
 //   32 x 16 (964 x 120: FP32 3.36 / 4.63, 32 x 8 in two rounds 3.9);
-//   64 x 16 (512^2: FP32 3.84 / 6.35, FP64 6.68 / 10.0), at E10 32 x 32.
+//   64 x 16 (512^2: FP32 3.84 / 6.35, FP64 6.68 / 10.0), in FP64 at E10 32 x 32.
 // Beyond, FP32 takes 64 x 16, the smallest halo share (2048^2 43.7 / 78.3, 8192^2
-// 638 / 1120); at E10 its LDS leaves one block per CU and 32 x 32 is ahead
-// (2048^2 48.9 / 63.5 for 64 x 16), except from 2^20 to 3 million nodes, where the
-// state half fits the last-level cache (1448^2: tile64x4r1 25.7, 32 x 32 28.3).
-// FP64 takes 32 x 16, two blocks per CU (2048^2
+// 638 / 1120; E10 1048^2 16.7 / 19.0, 1923^2 46.4 / 44.7, 2048^2 51.8 / 87.2, where
+// 32 x 32 takes 17.0, 51.9 and 65.9), but 32 x 32 at E10 while two rounds cover the
+// grid (1224 x 408: 8.3, 64 x 16 10.1).  FP64 takes 32 x 16, two blocks per CU (2048^2
 // 72.4 / 130); at E10 the 32 x 16 tile's 90 KB allow one: 32 x 32, except while
 // both copies of the state fit the last-level cache and the tiles leave most of
 // their last round of 256 empty, where the one-step tile32x8r1 is ahead (529^2, 289
@@ -475,14 +474,14 @@ static bool cache_resident(const sc_lbm_params& p)
 // 14.9 / 17.3; 2600 x 2100, out of it, FP64 114 / 98).
 static int auto_variant_d2q9(const sc_lbm_params& p, int64_t n)
 {
-    constexpr int kOne = 2, k64x4 = 3, k32x16 = 11, k64x16 = 13, k32x32 = 14, k32x8t1024 = 16, kK = 17;
-    const bool e10 = p.order == 10, cached = n >= (int64_t)1 << 20 && n < 3000000, d = p.precision == SC_FP64;
+    constexpr int kOne = 2, k32x16 = 11, k64x16 = 13, k32x32 = 14, k32x8t1024 = 16, kK = 17;
+    const bool e10 = p.order == 10, d = p.precision == SC_FP64;
     const int small = small_shape(p, false);
     if (small >= 0) return kK + small;
     if (tiles_of(p, 32, 8) <= 256) return k32x8t1024;
     if (p.order == 4 && cache_resident(p) && (d ? tiles_of(p, 64, 16) > 256 : n >= (int64_t)1 << 19)) return kK + kK2x16x16;
     if (tiles_of(p, 32, 16) <= 256) return k32x16;
-    if (!d) return !e10 || tiles_of(p, 64, 16) <= 256 ? k64x16 : (cached ? k64x4 : k32x32);
+    if (!d) return e10 && tiles_of(p, 64, 16) > 256 && tiles_of(p, 32, 32) <= 512 ? k32x32 : k64x16;
     if (e10) {
         const int64_t t = tiles_of(p, 32, 32);
         return t <= 256 || (t >= 400 && t <= 512) || !cache_resident(p) ? k32x32 : kOne;

@@ -15,6 +15,10 @@ from paper_1906_11027_amd import sc_lbm as B  # noqa: E402
     ("D2Q9", "guo", "fp64", 10, (504, 504), "tile2x32x32"), ("D2Q9", "guo", "fp64", 10, (529, 529), "tile32x8r1"),
     ("D2Q9", "guo", "fp64", 10, (567, 493), "tile32x8r1"), ("D2Q9", "guo", "fp64", 10, (640, 640), "tile2x32x32"),
     ("D2Q9", "guo", "fp64", 10, (721, 721), "tile32x8r1"), ("D2Q9", "guo", "fp64", 10, (2048, 2048), "tile2x32x32"),
+    # E10 in FP32: 64 x 16, 32 x 32 only where it fills two rounds
+    ("D2Q9", "guo", "fp32", 10, (500, 500), "tile2x64x16"), ("D2Q9", "guo", "fp32", 10, (1224, 408), "tile2x32x32"),
+    ("D2Q9", "guo", "fp32", 10, (774, 774), "tile2x64x16"), ("D2Q9", "guo", "fp32", 10, (1702, 1702), "tile2x64x16"),
+    ("D2Q9", "guo", "fp32", 10, (3331, 1110), "tile2x64x16"), ("D2Q9", "guo", "fp32", 10, (2048, 2048), "tile2x64x16"),
 ])
 def test_shape(lattice, forcing, prec, order, shape, name):
     h = B.sc_lbm_create(B.make_params(lattice, shape, order=order, precision=prec, forcing=forcing, tau=0.9))
