@@ -19,6 +19,8 @@ from paper_1906_11027_amd import sc_lbm as B  # noqa: E402
     ("D2Q9", "guo", "fp32", 10, (500, 500), "tile2x64x16"), ("D2Q9", "guo", "fp32", 10, (1224, 408), "tile2x32x32"),
     ("D2Q9", "guo", "fp32", 10, (774, 774), "tile2x64x16"), ("D2Q9", "guo", "fp32", 10, (1702, 1702), "tile2x64x16"),
     ("D2Q9", "guo", "fp32", 10, (3331, 1110), "tile2x64x16"), ("D2Q9", "guo", "fp32", 10, (2048, 2048), "tile2x64x16"),
+    # D2Q9 with the exact difference method: 64 x 16 at every order
+    ("D2Q9", "edm", "fp32", 10, (1732, 1732), "wide2x64x16t1024"), ("D2Q9", "edm", "fp32", 8, (1732, 1732), "wide2x64x16t1024"),
 ])
 def test_shape(lattice, forcing, prec, order, shape, name):
     h = B.sc_lbm_create(B.make_params(lattice, shape, order=order, precision=prec, forcing=forcing, tau=0.9))
