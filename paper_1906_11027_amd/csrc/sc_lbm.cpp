@@ -535,7 +535,7 @@ static int two_step_height(const sc_lbm_params& p, int reach)
 //   FP32 beyond: the tile with the smallest halo share that still leaves two
 //     blocks per CU (4096 x 3000: D2Q13 E6 64 x 12 166, D2Q25 E8 64 x 16 388 /
 //     535).  While the state sits in the last-level cache, D2Q25 from E6 (below
-//     1.5 million nodes) and D2Q13 E10 (3 million) run one step at a time: the
+//     1.5 million nodes) and D2Q13 E10 run one step at a time: the
 //     halo collisions cost more than the pass saved (1151 x 2081 D2Q13 E10: 44.6,
 //     two steps 54.4);
 //   FP64, D2Q9: as FP32 with the tiles that still fit;
@@ -573,7 +573,7 @@ static int auto_variant_wide(const sc_lbm_params& p, int64_t n)
         }
         if (cached4) return two16;
         if (p.lattice == SC_D2Q9) return t64x16t1024;   // E10 1732^2: 38.9, 64 x 12 42.5, one step 39.0
-        if (E == 10) return n < 3000000 ? one16 : t64x8;
+        if (E == 10) return cached ? one16 : t64x8t1024;   // 1702^2, out of the cache: 63.4, one16 107, one step 75.4
         return E == 4 ? t64x16t1024 : t64x12t768;
     }
     if (p.lattice == SC_D2Q25) {

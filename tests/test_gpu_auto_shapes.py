@@ -21,6 +21,9 @@ from paper_1906_11027_amd import sc_lbm as B  # noqa: E402
     ("D2Q9", "guo", "fp32", 10, (3331, 1110), "tile2x64x16"), ("D2Q9", "guo", "fp32", 10, (2048, 2048), "tile2x64x16"),
     # D2Q9 with the exact difference method: 64 x 16 at every order
     ("D2Q9", "edm", "fp32", 10, (1732, 1732), "wide2x64x16t1024"), ("D2Q9", "edm", "fp32", 8, (1732, 1732), "wide2x64x16t1024"),
+    # D2Q13 E10 in FP32: one step while both copies of the state fit the cache
+    ("D2Q13", "edm", "fp32", 10, (1516, 1516), "wideK1x16x16"), ("D2Q13", "edm", "fp32", 10, (1702, 1702), "wide2x64x8t1024"),
+    ("D2Q13", "edm", "fp32", 10, (2000, 2000), "wide2x64x8t1024"),
 ])
 def test_shape(lattice, forcing, prec, order, shape, name):
     h = B.sc_lbm_create(B.make_params(lattice, shape, order=order, precision=prec, forcing=forcing, tau=0.9))
