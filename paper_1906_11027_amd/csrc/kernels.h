@@ -14,10 +14,10 @@
 // Products and sums of the 2D steps fuse as they are written, within one
 // expression, and not as each kernel's surroundings happen to allow: a step
 // then rounds the same in every launch shape, so a run gives the same bits
-// however it is cut into launches of one and two steps.  (D3Q19 advances one
-// step in every shape; it keeps the compiler's choice, worth 2% at 128^3.)  The
-// batched sweep, the initial state and the observables keep the compiler's
-// choice too: they define SC_LBM_CONTRACT_FREELY.
+// however it is cut into launches of one and two steps.  Units that define
+// SC_LBM_CONTRACT_FREELY keep the compiler's choice: D3Q19, which advances one step
+// in every shape (worth 2% at 128^3 MRT E8 and 5 to 14% in SRT E4), the batched sweep, the
+// initial state and the observables.
 #ifndef SC_LBM_CONTRACT_FREELY
 #pragma clang fp contract(on)
 #endif
@@ -267,7 +267,6 @@ constexpr bool d2q9_opposite_pairs()
 static_assert(d2q9_opposite_pairs(), "D2Q9 velocity order: b and b + 2 must be opposite for b = 1, 2, 5, 6");
 
 // --------------------------------------------------------------- D3Q19 ----
-#pragma clang fp contract(fast)
 template <typename T>
 __device__ __forceinline__ T sum19(const T (&g)[19])
 {
@@ -419,10 +418,6 @@ __device__ __forceinline__ void collide_d3q19(T (&g)[19], T drho, T Fx, T Fy, T 
         g[0] += dm;
     }
 }
-
-#ifndef SC_LBM_CONTRACT_FREELY
-#pragma clang fp contract(on)
-#endif
 
 // LDS of a block on gfx950
 constexpr size_t kLdsBytes = 160 * 1024;

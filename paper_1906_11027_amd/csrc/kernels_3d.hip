@@ -16,8 +16,8 @@
 #include <algorithm>
 #include <cstdint>
 
+#define SC_LBM_CONTRACT_FREELY   // every shape advances one step: nothing to keep in line
 #include "kernels.h"
-#pragma clang fp contract(fast)   // every shape advances one step: nothing to keep in line
 
 namespace sclbm {
 
