@@ -534,14 +534,15 @@ static int two_step_height(const sc_lbm_params& p, int reach)
 //     even those take many rounds (143 x 2827: 12.8, two steps 15.3);
 //   FP32 beyond: the tile with the smallest halo share that still leaves two
 //     blocks per CU (4096 x 3000: D2Q13 E6 64 x 12 166, D2Q25 E8 64 x 16 388 /
-//     535).  While the state sits in the last-level cache, D2Q25 from E6 (below
-//     1.5 million nodes) and D2Q13 E10 run one step at a time: the
+//     535).  While the state sits in the last-level cache, D2Q25 from E6 and D2Q13
+//     E10 run one step at a time: the
 //     halo collisions cost more than the pass saved (1151 x 2081 D2Q13 E10: 44.6,
 //     two steps 54.4);
 //   FP64, D2Q9: as FP32 with the tiles that still fit;
 //   FP64, D2Q13: 64 x 8 or 64 x 12 while two rounds cover the grid (832 x 215 E8
 //     64 x 12 7.9 / 10.5), at E4 64 x 16 (800 x 600 15.2 / 19.4), and two steps
-//     again from 2^20 nodes (2623 x 508 E8: 54.1 / 55.4; 4096 x 3000 E6: 404 / 533);
+//     again out of the cache (1144^2 E8: 50.8 / 54.8; 4096 x 3000 E6: 404 / 533), at
+//     E4 from 2^20 nodes;
 //   FP64, D2Q25: from E6 only 32 x 4 fits, one step is ahead (4096 x 3000 E8:
 //     1068, two steps 1336).
 static int auto_variant_wide(const sc_lbm_params& p, int64_t n)
@@ -568,7 +569,8 @@ static int auto_variant_wide(const sc_lbm_params& p, int64_t n)
         }
         if (p.lattice == SC_D2Q25) {
             if (E == 4) return t64x8;
-            if (n < 1500000) return wide64 ? one16 : one64;
+            if (cached) return wide64 ? one16 : one64;
+            if (n < 1450000) return k128x16r2;   // E8 1166^2: 56.1, one64 66.4, two steps 57.4; E10 59.2, 70, 62.5
             return E == 10 ? t64x14t1024 : t64x16t1024;   // E10 8192^2: 2548, 64 x 12 2899
         }
         if (cached4) return two16;
@@ -580,7 +582,7 @@ static int auto_variant_wide(const sc_lbm_params& p, int64_t n)
         if (E == 4) return t32x8;
         if (E == 10) return n < (int64_t)1 << 19 ? one16 : (n < (int64_t)1 << 20 ? k64x16r2 : k64x8r2);
         if (n < (int64_t)1 << 18) return one16;
-        if (n < (int64_t)1 << 19) return wide64 ? k32x8r1 : (full16 ? k64x16r2 : one16);   // 129 x 2795: 28.3, one16 31.6
+        if (cached) return wide64 ? k32x8r1 : one16;   // E8 728^2: 41.1, one64 46.9; 68 x 8235: 43.6, one16 43.9, 64 x 8 62.2
         return wide64 ? k64x8r2 : one64;
     }
     if (p.lattice == SC_D2Q9) {
@@ -595,7 +597,7 @@ static int auto_variant_wide(const sc_lbm_params& p, int64_t n)
     if (t12 <= 256) return t64x12t768;
     if (E == 4 && t16 <= 512 && full16) return t64x16t1024;
     if (E < 10 && t8 <= 512) return t64x8t1024;
-    if (n < (int64_t)1 << 20) return one16;
+    if (n < (int64_t)1 << 20 || (cached && E > 4 && E < 10)) return one16;   // E8 1131^2: 46.6, 64 x 12 53.4
     if (E == 10 && n < 1500000) return k128x16r2;
     return E == 4 ? t32x8 : t64x12t768;
 }

@@ -24,6 +24,11 @@ from paper_1906_11027_amd import sc_lbm as B  # noqa: E402
     # D2Q13 E10 in FP32: one step while both copies of the state fit the cache
     ("D2Q13", "edm", "fp32", 10, (1516, 1516), "wideK1x16x16"), ("D2Q13", "edm", "fp32", 10, (1702, 1702), "wide2x64x8t1024"),
     ("D2Q13", "edm", "fp32", 10, (2000, 2000), "wide2x64x8t1024"),
+    # D2Q25 from E6 and D2Q13 E6, E8 in FP64: one step in the cache
+    ("D2Q25", "edm", "fp32", 8, (1148, 1148), "wideK1x64x8"), ("D2Q25", "edm", "fp32", 8, (1166, 1166), "wide128x16r2"),
+    ("D2Q25", "edm", "fp32", 8, (1216, 1216), "wide2x64x16t1024"), ("D2Q25", "edm", "fp64", 8, (728, 728), "wideK1x16x16"),
+    ("D2Q25", "edm", "fp64", 6, (68, 8235), "wide32x8r1"), ("D2Q25", "edm", "fp64", 8, (830, 830), "wideK1x64x8"),
+    ("D2Q13", "edm", "fp64", 8, (1131, 1131), "wideK1x16x16"), ("D2Q13", "edm", "fp64", 8, (1144, 1144), "wide2x64x12t768"),
 ])
 def test_shape(lattice, forcing, prec, order, shape, name):
     h = B.sc_lbm_create(B.make_params(lattice, shape, order=order, precision=prec, forcing=forcing, tau=0.9))
