@@ -407,6 +407,11 @@ static int64_t tiles_of(const sc_lbm_params& p, int tx, int ty)
     return (int64_t)((p.nx + tx - 1) / tx) * ((p.ny + ty - 1) / ty);
 }
 static double overhang(const sc_lbm_params& p, int tx) { return (double)((p.nx + tx - 1) / tx * tx) / p.nx; }
+// nodes that tiles of tx x ty cover, per node of the grid
+static double cover(const sc_lbm_params& p, int tx, int ty)
+{
+    return (double)tiles_of(p, tx, ty) * tx * ty / ((double)p.nx * p.ny);
+}
 
 // Tiles with one node per thread and K steps per launch, for grids that one
 // round of blocks covers: there a step costs the launch and a chain of
@@ -557,18 +562,33 @@ static int auto_variant_wide(const sc_lbm_params& p, int64_t n)
     const bool wide64 = overhang(p, 64) > 1.2;   // 64-wide columns hang over
     const bool cached = cache_resident(p), cached4 = E == 4 && p.lattice == SC_D2Q9 && cached;
     const bool full16 = t16 * 5 >= rounds16 * 256 * 4;   // no mostly empty last round of 64 x 16
+    // Strips, in the cache: a two-step tile pays for the nodes that hang over, a
+    // one-step tile hardly, and wide32x8r1 the least.  us per step, the two-step tile /
+    // the strip's shape: D2Q13 E8 FP32 70 x 12857 25.3 / 21.0, 24 x 16666 17.5 / 9.3; D2Q25 E4
+    // FP32 88 x 10227 36.8 / 32.3; D2Q9 E6 FP64 70 x 12857 34.1 / 23.3, 131 x 6870 29.3 /
+    // 23.3, 34 x 11764 (32 x 8) 18.7 / 14.3; D2Q13 E8 FP64 88 x 1704 10.6 / 9.6, 24 x 3333 10.3 /
+    // 7.6; D2Q25 E4 FP64 70 x 5714 (32 x 8) 37.1 / 31.0.  16-wide tiles that hang over by a third,
+    // and 32-wide ones no more, lose to wide32x8r1 too (D2Q25 E8 FP64 49 x 4489: 25.0 /
+    // 21.3), except at E10.
+    const bool strip = cached && overhang(p, 64) > 1.15;
+    const bool hang16 = overhang(p, 16) > 1.3 && overhang(p, 16) >= overhang(p, 32);
+    const int one = E < 10 && hang16 && n < (int64_t)1 << 20 ? k32x8r1 : one16;
+    if (cached && overhang(p, 64) > 2 && n >= (int64_t)1 << 17 && n < (int64_t)1 << 20 &&
+        !(cached4 && (p.precision == SC_FP64 || n >= (int64_t)1 << 19)))
+        return one;
     if (p.precision != SC_FP64) {
         if (n < (int64_t)1 << 19) {
             if (p.lattice == SC_D2Q25 && E == 10 && t8 > 256)   // 64 x 16 does not fit
                 return t12 <= 256 ? t64x12t768 : (wide64 ? one16 : one64);
-            if (p.lattice == SC_D2Q25 && E == 4 && t8 > 512) return t64x8;
-            if (E == 10 && wide64 && t8 > 256) return t8 <= 768 ? t32x8 : one16;
+            if (p.lattice == SC_D2Q25 && E == 4 && t8 > 512) return strip && n >= (int64_t)1 << 18 ? one : t64x8;
+            if (E == 10 && wide64 && t8 > 256) return t8 <= 768 && overhang(p, 32) <= 1.5 ? t32x8 : one16;
+            if (p.lattice == SC_D2Q13 && E > 4 && wide64 && n >= (int64_t)1 << 18) return one;
             if (p.lattice == SC_D2Q25 && E > 4 && wide64 && t8 > 256) return one16;   // 69 x 2285 E6: 9.8, 64 x 12 13.0
             const int ty = two_step_height(p, p.lattice == SC_D2Q9 ? 1 : 2);
             return ty == 8 ? t64x8t1024 : (ty == 12 ? t64x12t768 : t64x16t1024);
         }
         if (p.lattice == SC_D2Q25) {
-            if (E == 4) return t64x8;
+            if (E == 4) return strip && n < (int64_t)1 << 20 ? one : t64x8;
             if (cached) return wide64 ? one16 : one64;
             if (n < 1450000) return k128x16r2;   // E8 1166^2: 56.1, one64 66.4, two steps 57.4; E10 59.2, 70, 62.5
             return E == 10 ? t64x14t1024 : t64x16t1024;   // E10 8192^2: 2548, 64 x 12 2899
@@ -576,12 +596,13 @@ static int auto_variant_wide(const sc_lbm_params& p, int64_t n)
         if (cached4) return two16;
         if (p.lattice == SC_D2Q9) return t64x16t1024;   // E10 1732^2: 38.9, 64 x 12 42.5, one step 39.0
         if (E == 10) return cached ? one16 : t64x8t1024;   // 1702^2, out of the cache: 63.4, one16 107, one step 75.4
+        if (E > 4 && wide64 && cached) return one;
         return E == 4 ? t64x16t1024 : t64x12t768;
     }
     if (p.lattice == SC_D2Q25) {
-        if (E == 4) return t32x8;
+        if (E == 4) return cached && overhang(p, 32) > 1.08 ? k32x8r1 : t32x8;
         if (E == 10) return n < (int64_t)1 << 19 ? one16 : (n < (int64_t)1 << 20 ? k64x16r2 : k64x8r2);
-        if (n < (int64_t)1 << 18) return one16;
+        if (n < (int64_t)1 << 18) return one;
         if (cached) return wide64 ? k32x8r1 : one16;   // E8 728^2: 41.1, one64 46.9; 68 x 8235: 43.6, one16 43.9, 64 x 8 62.2
         return wide64 ? k64x8r2 : one64;
     }
@@ -591,13 +612,15 @@ static int auto_variant_wide(const sc_lbm_params& p, int64_t n)
         if (t16 <= 256) return t64x16t1024;
         if (cached4) return two16;
         if (E == 10) return cached ? one16 : t32x8;
+        if (E > 4 && cached && (n < (int64_t)1 << 19 ? overhang(p, 32) > 1.15 : strip)) return one;
         return E == 4 || n < (int64_t)1 << 19 ? t32x8 : t64x8;
     }
+    if (E > 4 && overhang(p, 64) > 2) return one;
     if (t8 <= 256) return t64x8t1024;
     if (t12 <= 256) return t64x12t768;
     if (E == 4 && t16 <= 512 && full16) return t64x16t1024;
-    if (E < 10 && t8 <= 512) return t64x8t1024;
-    if (n < (int64_t)1 << 20 || (cached && E > 4 && E < 10)) return one16;   // E8 1131^2: 46.6, 64 x 12 53.4
+    if (E < 10 && t8 <= 512 && !(E > 4 && wide64)) return t64x8t1024;
+    if (n < (int64_t)1 << 20 || (cached && E > 4 && E < 10)) return one;   // E8 1131^2: 46.6, 64 x 12 53.4
     if (E == 10 && n < 1500000) return k128x16r2;
     return E == 4 ? t32x8 : t64x12t768;
 }
@@ -621,16 +644,18 @@ static int one_step_wide(const sc_lbm_params& p, int64_t n)
 // cover the grid (320^2: D2Q13 E8 FP32 5.27 us per step, one step 5.57,
 // wide32x8r1 7.10; FP64 beyond E4 one step, 7.80 / 8.72), on D2Q9 and at E4 four
 // (512^2 D2Q25 E4 FP64 20.8, one step 23.1), and one step from there
-// (512^2 D2Q25 E8 FP32 13.1 / 14.7), on large grids one_step_wide()'s.
+// (512^2 D2Q25 E8 FP32 13.1 / 14.7), where 16 x 16 tiles do not hang over (5586 x 38 E8
+// FP32: 9.2, wide32x8r1 7.1), on large grids one_step_wide()'s.
 static int wall_shape(const sc_lbm_params& p, int64_t n)
 {
-    constexpr int kK = 15;
+    constexpr int k32x8r1 = 1, kK = 15;
     const int small = small_shape(p, true);
     if (small >= 0) return kK + small;
     if (n >= (int64_t)1 << 20) return one_step_wide(p, n);
     const bool d = p.precision == SC_FP64, light = p.lattice == SC_D2Q9 || p.order == 4;
     if (p.order == 4 && p.lattice == SC_D2Q9) return kK + kK2x16x16;
-    if (tiles_of(p, 16, 16) > (light ? 1024 : 512)) return kK + kK1x16x16;
+    if (tiles_of(p, 16, 16) > (light ? 1024 : 512))
+        return cover(p, 16, 16) > 1.1 * cover(p, 32, 8) ? k32x8r1 : kK + kK1x16x16;
     if (d && (p.order == 10 || (p.lattice == SC_D2Q13 && p.order > 4))) return kK + kK1x16x16;
     return kK + kK2x16x16;
 }

@@ -29,6 +29,14 @@ from paper_1906_11027_amd import sc_lbm as B  # noqa: E402
     ("D2Q25", "edm", "fp32", 8, (1216, 1216), "wide2x64x16t1024"), ("D2Q25", "edm", "fp64", 8, (728, 728), "wideK1x16x16"),
     ("D2Q25", "edm", "fp64", 6, (68, 8235), "wide32x8r1"), ("D2Q25", "edm", "fp64", 8, (830, 830), "wideK1x64x8"),
     ("D2Q13", "edm", "fp64", 8, (1131, 1131), "wideK1x16x16"), ("D2Q13", "edm", "fp64", 8, (1144, 1144), "wide2x64x12t768"),
+    # strips that the tiles hang over, and their neighbours that they do not
+    ("D2Q13", "edm", "fp32", 8, (70, 12857), "wideK1x16x16"), ("D2Q13", "edm", "fp32", 8, (24, 16666), "wide32x8r1"),
+    ("D2Q13", "edm", "fp32", 8, (192, 4700), "wide2x64x12t768"), ("D2Q25", "edm", "fp32", 4, (88, 10227), "wideK1x16x16"),
+    ("D2Q25", "edm", "fp32", 4, (128, 7000), "wide2x64x8t512"), ("D2Q9", "edm", "fp64", 6, (131, 6870), "wideK1x16x16"),
+    ("D2Q9", "edm", "fp64", 6, (34, 11764), "wideK1x16x16"), ("D2Q9", "edm", "fp64", 6, (128, 6870), "wide2x64x8t512"),
+    ("D2Q13", "edm", "fp64", 8, (88, 1704), "wideK1x16x16"), ("D2Q13", "edm", "fp64", 8, (24, 3333), "wide32x8r1"),
+    ("D2Q25", "edm", "fp64", 4, (70, 5714), "wide32x8r1"), ("D2Q25", "edm", "fp64", 4, (96, 5714), "wide2x32x8t256"),
+    ("D2Q25", "edm", "fp64", 8, (49, 4489), "wide32x8r1"),
 ])
 def test_shape(lattice, forcing, prec, order, shape, name):
     h = B.sc_lbm_create(B.make_params(lattice, shape, order=order, precision=prec, forcing=forcing, tau=0.9))

@@ -58,3 +58,12 @@ def test_large_d2q25_fp64_does_not_spill(order):
     assert np.array_equal(sim.state(), one.state())
     sim.close()
     one.close()
+
+
+def test_flat_channel_takes_tiles_that_fit():
+    """5586 x 38: 16 x 16 tiles cover a quarter more than the grid, 32 x 8 tiles 5%."""
+    for shape, name in (((5586, 38), "wide32x8r1"), ((5600, 48), "wideK1x16x16")):
+        sim = Sim(np.ones(shape), "D2Q9", order=8)
+        sim.set_walls(_channel(shape), 1.0)
+        assert sim.variant == name, (shape, sim.variant)
+        sim.close()
