@@ -208,8 +208,16 @@ k_d2q9_march(StepArgs<T> a, int H, int nbx)
     }
 }
 
+// Wavefronts per SIMD that a two-step tile is compiled for: what its block needs, and for
+// 1024 threads on 32 x 8 nodes in FP64 at E10 two blocks per CU, 64 registers (68 when
+// left alone: 2048^2 169 us per step, 127 with two blocks; 1516^2 100 and 79).
+constexpr int tile2_waves(size_t value, int order, int nodes, int nt)
+{
+    return nt == 1024 && nodes == 256 && order == 10 && value == 8 ? 8 : (nt + 255) / 256;
+}
+
 template <typename T, int ORDER, int TX, int TY, int NT>
-__global__ void __launch_bounds__(NT)
+__global__ void __launch_bounds__(NT, tile2_waves(sizeof(T), ORDER, TX* TY, NT))
 k_d2q9_tile2(StepArgs<T> a, int nbx, int nby, int sw)
 {
     using LD = Tile2Lds<Stencil<2, ORDER>::R, TX, TY>;

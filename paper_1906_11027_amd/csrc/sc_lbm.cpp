@@ -542,7 +542,9 @@ static int two_step_height(const sc_lbm_params& p, int reach)
 //     535).  While the state sits in the last-level cache, D2Q25 from E6 and D2Q13
 //     E10 run one step at a time: the
 //     halo collisions cost more than the pass saved (1151 x 2081 D2Q13 E10: 44.6,
-//     two steps 54.4);
+//     two steps 54.4; there wide128x16r2 from 2^20 nodes, 748 x 1902: 29.4, 16 x 16
+//     30.8, up to 2^21, 1450^2: 44.9 / 45.1, 1600^2: 62.9 / 50.7, and where 128-wide
+//     tiles do not hang over, 160 x 9000: 34.4 / 31.6);
 //   FP64, D2Q9: as FP32 with the tiles that still fit;
 //   FP64, D2Q13: 64 x 8 or 64 x 12 while two rounds cover the grid (832 x 215 E8
 //     64 x 12 7.9 / 10.5), at E4 64 x 16 (800 x 600 15.2 / 19.4), and two steps
@@ -595,7 +597,8 @@ static int auto_variant_wide(const sc_lbm_params& p, int64_t n)
         }
         if (cached4) return two16;
         if (p.lattice == SC_D2Q9) return t64x16t1024;   // E10 1732^2: 38.9, 64 x 12 42.5, one step 39.0
-        if (E == 10) return cached ? one16 : t64x8t1024;   // 1702^2, out of the cache: 63.4, one16 107, one step 75.4
+        if (E == 10 && cached) return n >= (int64_t)1 << 20 && n < (int64_t)1 << 21 && overhang(p, 128) < 1.15 ? k128x16r2 : one16;
+        if (E == 10) return t64x8t1024;   // 1702^2, out of the cache: 63.4, one16 107, one step 75.4
         if (E > 4 && wide64 && cached) return one;
         return E == 4 ? t64x16t1024 : t64x12t768;
     }

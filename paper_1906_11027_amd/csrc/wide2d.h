@@ -208,8 +208,21 @@ __device__ __forceinline__ void collide_lat(T (&g)[L::Q], T drho, T Fx, T Fy, co
 static_assert(has_opposite_pairs<D2Q9>() && has_opposite_pairs<D2Q13>() && has_opposite_pairs<D2Q25>(),
               "every moving velocity needs an opposite of equal weight");
 
+// Wavefronts per SIMD that a tile of NT threads is compiled for: what its block needs,
+// and for 128 x 16 tiles of 1024 threads in FP32 on D2Q13 with the widest stencil two
+// blocks per CU, 64 registers.  Left alone it takes 69 to 71, one block: 748 x 1902
+// 32.7 us per step against 29.4, 1516^2 51.9 against 45.5, 2048^2 115 to 119 against 109
+// to 119.  The 256 x 8 tiles spill more for it and lose beyond the cache (2048^2 109 us
+// left alone, 124 with two blocks).
+constexpr int wide_tile_waves(size_t value, int q, int order, bool walls, int nt, int ty)
+{
+    return nt == 1024 && ty == 16 && value == 4 && q == 13 && order == 10 && !walls
+               ? 8
+               : (nt + 255) / 256;
+}
+
 template <typename T, typename L, int ORDER, bool EDM, bool WALLS, int TX, int TY, int RPT>
-__global__ void __launch_bounds__(TX*(TY / RPT))
+__global__ void __launch_bounds__(TX*(TY / RPT), wide_tile_waves(sizeof(T), L::Q, ORDER, WALLS, TX*(TY / RPT), TY))
 k_wide_tile(StepArgs<T> a, int nbx, int nby, int sw)
 {
     using ST = Stencil<2, ORDER>;
