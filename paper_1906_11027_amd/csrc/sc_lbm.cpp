@@ -456,6 +456,16 @@ static bool cache_resident(const sc_lbm_params& p)
     return 2 * sc_lbm_state_bytes(&p) <= (size_t)1 << 28;
 }
 
+// In the cache, from 1.5 million nodes, fewer than 512 columns that no 64-wide tile
+// divides: the rows start off the tiles' alignment, and of at most eight tiles across one
+// hangs over.  Two-step tiles, which pull the widest halos, lose there to one step (over
+// 39 widths and 2 million nodes, D2Q9 E8 FP32: 0.84-0.99 of its time off the multiples of 64
+// and 1.05-1.15 at them; at 1.1 million nodes 1.05 on both, from 513 columns 1.04 and more).
+static bool narrow_off64(const sc_lbm_params& p, int64_t n)
+{
+    return p.nx < 512 && p.nx % 64 != 0 && n >= 1500000 && cache_resident(p);
+}
+
 // D2Q9 with Guo forcing, larger grids: the two-step tiles, which read and write the state
 // once per two steps and halve the launches.  us per step, E8 unless marked,
 // against the one-step shapes that were taken before (tile32x8r1 below 2^20
@@ -476,16 +486,19 @@ static bool cache_resident(const sc_lbm_params& p)
 // 416, 507: 16.7 / 15.1; 1001 x 777: 20.5, against 24.8 for the best two-step
 // shape; 666 x 2953, just out of the cache, 80 / 58).  E4 takes the light 16 x 16 tiles with one
 // node per thread in the cache (1500 x 1100: FP64 23.5, the shapes above 32.5; FP32
-// 14.9 / 17.3; 2600 x 2100, out of it, FP64 114 / 98).
+// 14.9 / 17.3; 2600 x 2100, out of it, FP64 114 / 98).  FP32 strips of narrow_off64() take
+// one step of 64 x 16 (E8 451 x 5276 27.6, two steps 31.6; 313 x 10523 35.2 / 37.3; 84 x
+// 35714 0.81 of it; E6 451 x 5276 27.3 / 30.2, E10 313 x 10523 36.7 / 39.8).
 static int auto_variant_d2q9(const sc_lbm_params& p, int64_t n)
 {
-    constexpr int kOne = 2, k32x16 = 11, k64x16 = 13, k32x32 = 14, k32x8t1024 = 16, kK = 17;
+    constexpr int kOne64 = 0, kOne = 2, k32x16 = 11, k64x16 = 13, k32x32 = 14, k32x8t1024 = 16, kK = 17;
     const bool e10 = p.order == 10, d = p.precision == SC_FP64;
     const int small = small_shape(p, false);
     if (small >= 0) return kK + small;
     if (tiles_of(p, 32, 8) <= 256) return k32x8t1024;
     if (p.order == 4 && cache_resident(p) && (d ? tiles_of(p, 64, 16) > 256 : n >= (int64_t)1 << 19)) return kK + kK2x16x16;
     if (tiles_of(p, 32, 16) <= 256) return k32x16;
+    if (!d && narrow_off64(p, n)) return kOne64;
     if (!d) return e10 && tiles_of(p, 64, 16) > 256 && tiles_of(p, 32, 32) <= 512 ? k32x32 : k64x16;
     if (e10) {
         const int64_t t = tiles_of(p, 32, 32);
@@ -596,6 +609,9 @@ static int auto_variant_wide(const sc_lbm_params& p, int64_t n)
             return E == 10 ? t64x14t1024 : t64x16t1024;   // E10 8192^2: 2548, 64 x 12 2899
         }
         if (cached4) return two16;
+        // strips, E8: 451 x 5276 30.0, two steps 31.6; E6 210 x 17276 41.3 / 46.4, 451 x 3325, below two million nodes,
+        // 1.08; where 128-wide tiles hang over further than 64-wide ones, 388 x 5154, two steps are 1.10 faster
+        if (p.lattice == SC_D2Q9 && n >= 2000000 && narrow_off64(p, n) && overhang(p, 128) == overhang(p, 64)) return k128x16r2;
         if (p.lattice == SC_D2Q9) return t64x16t1024;   // E10 1732^2: 38.9, 64 x 12 42.5, one step 39.0
         if (E == 10 && cached) return n >= (int64_t)1 << 20 && n < (int64_t)1 << 21 && overhang(p, 128) < 1.15 ? k128x16r2 : one16;
         if (E == 10) return t64x8t1024;   // 1702^2, out of the cache: 63.4, one16 107, one step 75.4

@@ -39,6 +39,11 @@ from paper_1906_11027_amd import sc_lbm as B  # noqa: E402
     ("D2Q13", "edm", "fp64", 8, (88, 1704), "wideK1x16x16"), ("D2Q13", "edm", "fp64", 8, (24, 3333), "wide32x8r1"),
     ("D2Q25", "edm", "fp64", 4, (70, 5714), "wide32x8r1"), ("D2Q25", "edm", "fp64", 4, (96, 5714), "wide2x32x8t256"),
     ("D2Q25", "edm", "fp64", 8, (49, 4489), "wide32x8r1"),
+    # D2Q9 strips off the multiples of 64, from 1.5 million nodes
+    ("D2Q9", "guo", "fp32", 8, (451, 5276), "tile64x16r4"), ("D2Q9", "guo", "fp32", 8, (448, 5276), "tile2x64x16"),
+    ("D2Q9", "guo", "fp32", 10, (313, 10523), "tile64x16r4"), ("D2Q9", "guo", "fp32", 6, (513, 4745), "tile2x64x16"),
+    ("D2Q9", "guo", "fp32", 8, (451, 2400), "tile2x64x16"), ("D2Q9", "guo", "fp32", 8, (451, 9000), "tile2x64x16"),
+    ("D2Q9", "edm", "fp32", 6, (210, 17276), "wide128x16r2"), ("D2Q9", "edm", "fp32", 8, (388, 5154), "wide2x64x16t1024"),
 ])
 def test_shape(lattice, forcing, prec, order, shape, name):
     h = B.sc_lbm_create(B.make_params(lattice, shape, order=order, precision=prec, forcing=forcing, tau=0.9))
