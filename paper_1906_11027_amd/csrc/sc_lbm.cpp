@@ -556,7 +556,7 @@ static int two_step_height(const sc_lbm_params& p, int reach)
 //     E10 run one step at a time: the
 //     halo collisions cost more than the pass saved (1151 x 2081 D2Q13 E10: 44.6,
 //     two steps 54.4; there wide128x16r2 from 2^20 nodes, 748 x 1902: 29.4, 16 x 16
-//     30.8, up to 2^21, 1450^2: 44.9 / 45.1, 1600^2: 62.9 / 50.7, and where 128-wide
+//     30.8, 958 x 2298: 42.2 / 44.3, not far beyond, 1500^2: 44.8 / 44.4, 1600^2: 62.9 / 50.7, and where 128-wide
 //     tiles do not hang over, 160 x 9000: 34.4 / 31.6);
 //   FP64, D2Q9: as FP32 with the tiles that still fit;
 //   FP64, D2Q13: 64 x 8 or 64 x 12 while two rounds cover the grid (832 x 215 E8
@@ -613,7 +613,7 @@ static int auto_variant_wide(const sc_lbm_params& p, int64_t n)
         // 1.08; where 128-wide tiles hang over further than 64-wide ones, 388 x 5154, two steps are 1.10 faster
         if (p.lattice == SC_D2Q9 && n >= 2000000 && narrow_off64(p, n) && overhang(p, 128) == overhang(p, 64)) return k128x16r2;
         if (p.lattice == SC_D2Q9) return t64x16t1024;   // E10 1732^2: 38.9, 64 x 12 42.5, one step 39.0
-        if (E == 10 && cached) return n >= (int64_t)1 << 20 && n < (int64_t)1 << 21 && overhang(p, 128) < 1.15 ? k128x16r2 : one16;
+        if (E == 10 && cached) return n >= (int64_t)1 << 20 && n < 2250000 && overhang(p, 128) < 1.15 ? k128x16r2 : one16;
         if (E == 10) return t64x8t1024;   // 1702^2, out of the cache: 63.4, one16 107, one step 75.4
         if (E > 4 && wide64 && cached) return one;
         return E == 4 ? t64x16t1024 : t64x12t768;

@@ -24,8 +24,8 @@ from paper_1906_11027_amd import sc_lbm as B  # noqa: E402
     # D2Q13 E10 in FP32: one step while both copies of the state fit the cache
     ("D2Q13", "edm", "fp32", 10, (1516, 1516), "wideK1x16x16"), ("D2Q13", "edm", "fp32", 10, (1702, 1702), "wide2x64x8t1024"),
     ("D2Q13", "edm", "fp32", 10, (2000, 2000), "wide2x64x8t1024"),
-    ("D2Q13", "edm", "fp32", 10, (748, 1902), "wide128x16r2"), ("D2Q13", "guo", "fp32", 10, (1448, 1448), "wide128x16r2"),
-    ("D2Q13", "edm", "fp32", 10, (1449, 1449), "wideK1x16x16"), ("D2Q13", "edm", "fp32", 10, (160, 9000), "wideK1x16x16"),
+    ("D2Q13", "edm", "fp32", 10, (748, 1902), "wide128x16r2"), ("D2Q13", "guo", "fp32", 10, (958, 2298), "wide128x16r2"),
+    ("D2Q13", "edm", "fp32", 10, (1500, 1500), "wideK1x16x16"), ("D2Q13", "edm", "fp32", 10, (160, 9000), "wideK1x16x16"),
     # D2Q25 from E6 and D2Q13 E6, E8 in FP64: one step in the cache
     ("D2Q25", "edm", "fp32", 8, (1148, 1148), "wideK1x64x8"), ("D2Q25", "edm", "fp32", 8, (1166, 1166), "wide128x16r2"),
     ("D2Q25", "edm", "fp32", 8, (1216, 1216), "wide2x64x16t1024"), ("D2Q25", "edm", "fp64", 8, (728, 728), "wideK1x16x16"),
