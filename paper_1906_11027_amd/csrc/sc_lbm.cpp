@@ -673,9 +673,11 @@ static int wall_shape(const sc_lbm_params& p, int64_t n)
     if (n >= (int64_t)1 << 20) return one_step_wide(p, n);
     const bool d = p.precision == SC_FP64, light = p.lattice == SC_D2Q9 || p.order == 4;
     if (p.order == 4 && p.lattice == SC_D2Q9) return kK + kK2x16x16;
-    if (tiles_of(p, 16, 16) > (light ? 1024 : 512))
-        return cover(p, 16, 16) > 1.1 * cover(p, 32, 8) ? k32x8r1 : kK + kK1x16x16;
-    if (d && (p.order == 10 || (p.lattice == SC_D2Q13 && p.order > 4))) return kK + kK1x16x16;
+    const int64_t t16 = tiles_of(p, 16, 16);
+    const double hang = cover(p, 16, 16) / cover(p, 32, 8);
+    if (t16 > (light ? 1024 : 512)) return hang > 1.1 ? k32x8r1 : kK + kK1x16x16;
+    if (d && (p.order == 10 || (p.lattice == SC_D2Q13 && p.order > 4)))
+        return t16 > 512 && hang > 1.15 ? k32x8r1 : kK + kK1x16x16;   // 2760 x 33 D2Q9 E10: 8.59, 16 x 16 10.5
     return kK + kK2x16x16;
 }
 

@@ -67,3 +67,12 @@ def test_flat_channel_takes_tiles_that_fit():
         sim.set_walls(_channel(shape), 1.0)
         assert sim.variant == name, (shape, sim.variant)
         sim.close()
+
+
+def test_fp64_strips_that_16_rows_hang_over():
+    """33 rows: 16 x 16 tiles cover 48 of them, 8-row tiles 40."""
+    shape = (2760, 33)
+    sim = Sim(np.ones(shape), "D2Q9", order=10, tau=0.9, precision="fp64")
+    sim.set_walls(_channel(shape), 1.0)
+    assert sim.variant == "wide32x8r1", sim.variant
+    sim.close()
