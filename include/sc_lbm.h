@@ -404,7 +404,8 @@ int sc_nn_conv3x3_fwd(const float* in, const uint16_t* w, const float* bias, flo
                       int32_t cin, int32_t cout, int32_t h, int32_t wd, void* stream);
 
 /* Gradient w.r.t. the input (cin must be 32): gin = conv(gout, w flipped and
- * transposed); wt_scratch holds cin*cout*9 bfloat16. */
+ * transposed).  wt_scratch must not be NULL; it is neither read nor written (the
+ * kernels take the weights in that order from w itself). */
 int sc_nn_conv3x3_bwd_data(const float* gout, const uint16_t* w, uint16_t* wt_scratch, float* gin, int32_t batch,
                            int32_t cin, int32_t cout, int32_t h, int32_t wd, void* stream);
 

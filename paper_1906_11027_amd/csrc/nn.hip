@@ -508,10 +508,12 @@ struct PairStage {
 // Layers with fewer than 32 channels on either side: FP32 16 x 16 x 4 MFMAs, k
 // running over 4 consecutive pixels of a tile row.  NB waves per partial row,
 // one per (co, ci) block, 4 / NB rows per block of four waves.
-// What bounds it: the FP32 matrix rate, 36 MFMAs of 32 cycles per tile row and
-// wave; 5 -> 32 channels at batch 16, 256 x 256 108 us (150 with tiles staged by
-// the whole block between two barriers), 32 -> 1 105 (197).  Each accumulator
-// adds its products in the same order as then.
+// What bounds it: latency beside the FP32 matrix rate.  36 MFMAs of 32 cycles per
+// tile row and wave are 61 us at batch 16, 256 x 256 (2.4 GHz), 0.57 of the 106
+// that 5 -> 32 and 32 -> 1 channels take; with one wave per SIMD nothing covers the
+// loads, the patch and the bias sums (6 us).  Tiles staged by the whole block
+// between two barriers took 150 and 197 us.  Each accumulator adds its products,
+// and the bias its gradients, in the same order as then.
 template <int NB, int EDGE>
 __global__ void __launch_bounds__(256)
 k_conv_bwd_w(const float* __restrict__ in, const float* __restrict__ gout, float* __restrict__ partial, int nblk,
@@ -672,10 +674,11 @@ k_conv_bwd_w(const float* __restrict__ in, const float* __restrict__ gout, float
 // 256 x 256).
 //
 // What bounds it: vector issue and the matrix cores, 224 VALU instructions
-// beside 54 MFMAs per step and wave.  At batch 16, 256 x 256 it takes 135 - 147
+// beside 54 MFMAs per step and wave.  At batch 16, 256 x 256 it takes 128 - 138
 // us, where staging the parts of a whole tile through block-wide LDS took 223
 // (16-bit stores, one block per CU).  Every accumulator sums the same products
-// in the same order as that kernel did, so the gradients are the same to the bit.
+// in the same order as that kernel did, so the weight gradients are the same to the
+// bit; the bias gradients are summed in another order, in shorter chains.
 constexpr int kWGroups = 2;                    // partial rows a block works on
 
 template <int EDGE>
@@ -1049,7 +1052,8 @@ static int cu_count()
     return cache[dev];
 }
 
-// the MFMA kernels address an image's channels with 32-bit element offsets
+// 32 planes of an image hold fewer than 2^31 values (planes are addressed in 64
+// bits, pixels, tiles and units counted in 32)
 static bool conv_shape_ok(int batch, int cin, int cout, int h, int w)
 {
     return batch >= 1 && cin >= 1 && cin <= MAXC && (cout == 1 || cout == MAXC) && h >= 1 && w >= 1 &&

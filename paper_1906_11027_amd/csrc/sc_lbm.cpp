@@ -23,11 +23,13 @@ using namespace sclbm;
 namespace {
 
 constexpr int kGraphSteps = 32;   // steps per captured graph (even)
-// automatic batched launch shapes (batch_shape_*), two steps per launch:
-// FP32 on 32 x 16 tiles with 512 threads (72.7 GLUPS on the 64-droplet
-// sweep, against 63 for the 64 x 16 and 32 x 8 tiles), FP64 on 64 x 16
-// tiles with 1024 threads (34.5 GLUPS, against 28-29 for 32 x 8 and
-// 32 x 16); sc_lbm_batch_autotune measures them all
+// automatic batched launch shapes (batch_shape_*), two steps per launch: FP32
+// on 32 x 16 tiles with 512 threads, FP64 on 64 x 16 with 1024.  us per step,
+// sides of 64 to 128 / 128 to 256 / 256 to 512, 24 items a sweep:
+//   FP32  32 x 16 5.6 / 12.0 / 33.2, 64 x 16 6.6 / 11.7 / 31.2, 32 x 8 6.2 / 13.9 / 39.0
+//   FP64  64 x 16 11.2 / 23.6 / 94.8, 32 x 16 11.5 / 28.9 / 121, 32 x 8 10.8 / 28.2 / 118
+// No FP32 shape wins everywhere: 32 x 16 is up to 15% ahead on small items, 64 x 16
+// up to 13% on 64 large ones.  sc_lbm_batch_autotune measures them all.
 constexpr int kBatchShapeFP32 = 3;
 constexpr int kBatchShapeFP64 = 2;
 constexpr int kFloorWindow = 50;   // checks the FP32 resolution rule fits a line to
@@ -553,11 +555,11 @@ static int two_step_height(const sc_lbm_params& p, int reach)
 //   FP32 beyond: the tile with the smallest halo share that still leaves two
 //     blocks per CU (4096 x 3000: D2Q13 E6 64 x 12 166, D2Q25 E8 64 x 16 388 /
 //     535).  While the state sits in the last-level cache, D2Q25 from E6 and D2Q13
-//     E10 run one step at a time: the
-//     halo collisions cost more than the pass saved (1151 x 2081 D2Q13 E10: 44.6,
-//     two steps 54.4; there wide128x16r2 from 2^20 nodes, 748 x 1902: 29.4, 16 x 16
-//     30.8, 958 x 2298: 42.2 / 44.3, not far beyond, 1500^2: 44.8 / 44.4, 1600^2: 62.9 / 50.7, and where 128-wide
-//     tiles do not hang over, 160 x 9000: 34.4 / 31.6);
+//     E10 run one step at a time: the halo collisions cost more than the pass saved
+//     (1151 x 2081 D2Q13 E10: 44.6, two steps 54.4).  D2Q13 E10 takes wide128x16r2 from
+//     2^20 nodes (748 x 1902: 29.4, 16 x 16 30.8; 958 x 2298: 42.2 / 44.3; beyond, 1500^2
+//     44.8 / 44.4 and 1600^2 62.9 / 50.7) where 128-wide tiles hardly hang over (160 x 9000:
+//     34.4 / 31.6);
 //   FP64, D2Q9: as FP32 with the tiles that still fit;
 //   FP64, D2Q13: 64 x 8 or 64 x 12 while two rounds cover the grid (832 x 215 E8
 //     64 x 12 7.9 / 10.5), at E4 64 x 16 (800 x 600 15.2 / 19.4), and two steps

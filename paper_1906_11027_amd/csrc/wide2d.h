@@ -570,7 +570,7 @@ static hipError_t launch_wide_shape(const StepArgs<T>& a, int variant, hipStream
     case 19: return launch_tile_steps<T, WideModel<L, EDM>, ORDER, WALLS, 16, 16, 2>(a, s);
     case 20: return launch_tile_steps<T, WideModel<L, EDM>, ORDER, WALLS, 16, 16, 1>(a, s);
     case 21: return launch_tile_steps<T, WideModel<L, EDM>, ORDER, WALLS, 64, 8, 1>(a, s);
-    // the largest two-step tile that D2Q25 E10 fits in FP32 (158 KB of LDS)
+    // for D2Q25 E10 in FP32, where 64 x 16 does not fit (155,200 bytes of LDS)
     case 22:
         if constexpr (!WALLS) return launch_wide_tile2<T, L, ORDER, EDM, 64, 14, 1024>(a, s);
         return hipErrorInvalidValue;
